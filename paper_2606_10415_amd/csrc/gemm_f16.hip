@@ -61,6 +61,8 @@ namespace {
 //       kpos(c, k) = ((c >> 2) ^ (k & 3)) * 4 + ((c & 3) ^ 2 * ((k >> 3) & 1)):
 //       the transpose reads of one MFMA operand (4 k-rows x 32 bytes per
 //       16-lane group, groups 8 k-rows apart) then hit every bank once.
+//       With R = 64 a k-row is half the banks wide: k's parity picks the
+//       half, and chunk pair c >> 1 sits at (c >> 1) ^ (k bit 1, k bit 3).
 // Both are filled by direct global -> LDS loads issued as opaque
 // instructions, so the caller orders them with explicit vmcnt waits.
 template <int R, int BK, bool KC, int NT, bool PAIRED = false, int PB = 32>
@@ -78,6 +80,7 @@ struct Operand {
   __device__ static __forceinline__ int swz(int r) { return (r / (16 / CPR)) & (CPR - 1); }
   // !KC chunk position; an involution in c for fixed k
   __device__ static __forceinline__ int kpos(int c, int k) {
+    if constexpr (R == 64) return c ^ ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1);
     return (((c >> 2) ^ (k & 3)) << 2) | ((c & 3) ^ (((k >> 3) & 1) << 1));
   }
 
@@ -307,25 +310,41 @@ __device__ __forceinline__ void xfence(u32x2& a, u32x2& b) {
 // keep a value's registers allocated up to this point
 __device__ __forceinline__ void xkeep(const half8& a) { asm volatile("" ::"v"(a)); }
 __device__ __forceinline__ void xkeep(const u32x2& a, const u32x2& b) { asm volatile("" ::"v"(a), "v"(b)); }
-// read q of a 4-wave step: fragments in the order B0, A0, B1..B7, A1..A7,
+// read q of a 4-wave step: fragments in the order B0, A0, B1.., A1..,
 // ra (rb) reads per A (B) fragment; op 0 = A, 1 = B
 struct X4Rd {
   int op, f, h;
 };
-constexpr X4Rd x4_read(int q, int ra, int rb) {
-  for (int e = 0; e < 16; ++e) {
-    const int op = e == 0 ? 1 : e == 1 ? 0 : e <= 8 ? 1 : 0;
-    const int f = e <= 1 ? 0 : e <= 8 ? e - 1 : e - 8;
+constexpr X4Rd x4_read(int q, int tm, int tn, int ra, int rb) {
+  for (int e = 0; e < tm + tn; ++e) {
+    const int op = e == 0 ? 1 : e == 1 ? 0 : e <= tn ? 1 : 0;
+    const int f = e <= 1 ? 0 : e <= tn ? e - 1 : e - tn;
     const int n = op ? rb : ra;
     if (q < n) return X4Rd{op, f, q};
     q -= n;
   }
   return X4Rd{-1, 0, 0};
 }
-// reads issued after MFMA idx of a step: [x4_q0(idx), x4_q0(idx + 1))
-constexpr int x4_q0(int idx, int nrd) {
-  const int q = idx < 2 ? 0 : ((idx - 2) * nrd + 47) / 48;
+// Schedule of a 4-wave step of nm MFMAs: the slice barrier (second step)
+// comes after MFMA x4_bar; the reads of the next step are spread over x4_win
+// MFMAs from x4_beg on (second step: behind the barrier).  64 MFMAs per step
+// leave room for a wide window; a shorter step needs its reads out early.
+constexpr int x4_bar(int nm) { return nm >= 64 ? 1 : nm >= 32 ? 3 : nm >= 16 ? 1 : 1; }
+constexpr int x4_beg(int nm, int s) { return s == 1 || nm >= 64 ? x4_bar(nm) + 1 : nm >= 16 ? 1 : 0; }
+constexpr int x4_win(int nm) { return nm >= 64 ? 48 : nm >= 32 ? 20 : nm >= 16 ? 4 : 2; }
+// reads issued before MFMA idx of a step on set s
+constexpr int x4_q0(int idx, int nrd, int nm, int s) {
+  const int b = x4_beg(nm, s), w = x4_win(nm);
+  const int q = idx < b ? 0 : ((idx - b) * nrd + w - 1) / w;
   return q < nrd ? q : nrd;
+}
+// direct loads issued before the slot after MFMA idx: n, spread over the
+// MFMAs from the barrier on
+constexpr int x4_l0(int idx, int n, int nm) {
+  const int b = x4_bar(nm), wide = nm / n, tight = (nm - b) / n;
+  const int step = b + (n - 1) * wide < nm ? wide : tight > 0 ? tight : 1;
+  const int q = idx <= b ? 0 : (idx - b + step - 1) / step;
+  return idx >= nm ? n : q < n ? q : n;
 }
 // LDS read of a K-contiguous fragment
 template <int OFF>
@@ -446,20 +465,29 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
   };
   constexpr bool ragged_k = KFIX;
 
-  constexpr bool X4 = NT == 256 && BM == 256 && BN == 256 && EPI <= 3 && !RK && BK == 64 && NS == 2;
+  constexpr bool X4 = NT == 256 && BK == 64 && !RK && EPI <= 3;
   if constexpr (X4) {
-    // One wave per SIMD, 128x128 wave tiles, accumulators in AGPRs.  Every
+    // One wave per SIMD, 2x2 wave grid, accumulators in AGPRs.  Every
     // fragment read, MFMA and counter wait of the loop is an ordered asm
     // statement: a step's MFMAs run on one register set while the reads of
-    // the next step fill the other, all issued in the step's first 48 MFMAs;
-    // after the slice barrier the 16 direct loads of slice kt+2 are spread
-    // over the step's MFMAs.
-    static_assert(TM == 8 && TN == 8 && STAGE == 65536 && OA::BYTES == 32768, "X4 shape");
+    // the next step fill the other; after the slice barrier the direct loads
+    // of slice kt+NS are spread over the step's MFMAs.
+    //   256x256 tiles: two 64 KiB LDS stages; 16 loads, 128 MFMAs a slice, so
+    //     one slice of lead covers the load latency.  Slices run in pairs, so
+    //     that both stage offsets are compile-time constants.
+    //   smaller tiles: a slice is 1/2 to 1/16 of that work, so the LDS holds
+    //     3 to 8 stages instead and loads run NS - 1 slices ahead; the stage is a
+    //     uniform offset, added to the fragment addresses once per step.
     constexpr bool AK = !TA, BKC = TB;           // K-contiguous operands (row reads)
+    constexpr bool DYN = NS > 2;
+    static_assert(DYN || (BM == 256 && BN == 256), "two stages: 256x256 tiles");
+    static_assert(NS * STAGE <= 160 * 1024 && NS * PER_SLICE <= 63, "stages");
     constexpr int XRA = AK ? 1 : 2, XRB = BKC ? 1 : 2;
-    constexpr int NRD = 8 * (XRA + XRB);        // LDS reads per step
-    half8 xa[2][8], xb[2][8];                  // fragments of K-contiguous operands
-    u32x2 ta[2][8][2], tb[2][8][2];            // ... of k-major ones (two transpose reads)
+    constexpr int NRD = TM * XRA + TN * XRB;    // LDS reads per step
+    constexpr int NM = TM * TN;                 // MFMAs per step
+    constexpr int BAR = x4_bar(NM);
+    half8 xa[2][TM], xb[2][TN];                // fragments of K-contiguous operands
+    u32x2 ta[2][TM][2], tb[2][TN][2];          // ... of k-major ones (two transpose reads)
     const uint32_t sbase = (uint32_t)(uintptr_t)smem;
     // K-contiguous: fragment f of k-step kk at r[stage][kk] + 2048 f
     auto lterm = [&](int kk) {
@@ -467,50 +495,81 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
       const int c = kk * 4 + (lane >> 4);
       return (uint32_t)(r * 128 + ((c ^ (r >> 1)) << 4));
     };
-    // k-major: read h of fragment f, k-step kk at z[stage][f] + 16384 kk + 2048 h
-    // (the fragment's XOR-swizzled position differs per lane only in address
-    // bits 5..7, which no other term touches)
-    auto yterm = [&](int wx) {
-      const int kl = (lane >> 2) & 3, g1 = (lane >> 4) & 1;
-      return (uint32_t)(((8 * (lane >> 4) + kl) * 512 + 256 * wx + 16 * ((lane & 3) >> 1) + 8 * (lane & 1)) |
-                        (kl << 6) | (g1 << 5));
+    // k-major: read h of fragment f, k-step kk at z[stage][f] + 64 R kk + 8 R h
+    // for R rows (the fragment's XOR-swizzled position differs per lane only
+    // in address bits 5..7, which no other term touches); rb = first row
+    auto zaddr = [&](auto R_, int rb) {
+      constexpr int R = decltype(R_)::value;
+      const uint32_t kl = (lane >> 2) & 3, g1 = (lane >> 4) & 1;
+      const uint32_t k = 8 * (lane >> 4) + kl;
+      const uint32_t x = 16 * ((lane & 3) >> 1) + 8 * (lane & 1);
+      if constexpr (R == 64)
+        return k * 128 + (((uint32_t)(rb >> 4) ^ ((kl >> 1) | (g1 << 1))) << 5) + x;
+      else
+        return k * (2 * R) + 256 * (uint32_t)(rb >> 7) +
+               ((((uint32_t)((rb >> 5) & 3) ^ kl) << 6) | (((uint32_t)((rb >> 4) & 1) ^ g1) << 5)) + x;
     };
-    uint32_t ra[2][2], rb[2][2], za[2][8], zb[2][8];
+    constexpr int NP = DYN ? 1 : 2;             // stages with addresses of their own
+    uint32_t ra[NP][2], rb[NP][2], za[NP][TM], zb[NP][TN];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; p < NP; ++p) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        ra[p][kk] = sbase + p * STAGE + wm * 16384 + lterm(kk);
-        rb[p][kk] = sbase + p * STAGE + OA::BYTES + wn * 16384 + lterm(kk);
+        ra[p][kk] = sbase + p * STAGE + wm * (WTM * 128) + lterm(kk);
+        rb[p][kk] = sbase + p * STAGE + OA::BYTES + wn * (WTN * 128) + lterm(kk);
       }
 #pragma unroll
-      for (int f = 0; f < 8; ++f) {
-        const uint32_t cf = ((f >> 1) << 6) | ((f & 1) << 5);
-        za[p][f] = (sbase + p * STAGE + yterm(wm)) ^ cf;
-        zb[p][f] = (sbase + p * STAGE + OA::BYTES + yterm(wn)) ^ cf;
-      }
+      for (int f = 0; f < TM; ++f)
+        za[p][f] = sbase + p * STAGE + zaddr(std::integral_constant<int, BM>{}, wm * WTM + 16 * f);
+#pragma unroll
+      for (int f = 0; f < TN; ++f)
+        zb[p][f] = sbase + p * STAGE + OA::BYTES + zaddr(std::integral_constant<int, BN>{}, wn * WTN + 16 * f);
     }
-    // read q of the step into set D, from stage P, k-step KK
-    auto xread = [&](auto Q_, auto D_, auto P_, auto KK_) __attribute__((always_inline)) {
-      constexpr X4Rd r = x4_read(decltype(Q_)::value, XRA, XRB);
-      constexpr int D = decltype(D_)::value, P = decltype(P_)::value, KK = decltype(KK_)::value;
+    // read q of the step into set D, from stage P (DYN: from the stage at
+    // offset so), k-step KK
+    auto xread = [&](auto Q_, auto D_, auto P_, auto KK_, uint32_t so) __attribute__((always_inline)) {
+      constexpr X4Rd r = x4_read(decltype(Q_)::value, TM, TN, XRA, XRB);
+      constexpr int D = decltype(D_)::value, P = DYN ? 0 : decltype(P_)::value, KK = decltype(KK_)::value;
       if constexpr (r.op == 0) {
-        if constexpr (AK) xrd<r.f * 2048>(xa[D][r.f], ra[P][KK]);
-        else xrd_tr<KK * 16384 + r.h * 2048>(ta[D][r.f][r.h], za[P][r.f]);
+        if constexpr (AK) xrd<r.f * 2048>(xa[D][r.f], DYN ? ra[P][KK] + so : ra[P][KK]);
+        else xrd_tr<KK * 64 * BM + r.h * 8 * BM>(ta[D][r.f][r.h], DYN ? za[P][r.f] + so : za[P][r.f]);
       } else {
-        if constexpr (BKC) xrd<r.f * 2048>(xb[D][r.f], rb[P][KK]);
-        else xrd_tr<KK * 16384 + r.h * 2048>(tb[D][r.f][r.h], zb[P][r.f]);
+        if constexpr (BKC) xrd<r.f * 2048>(xb[D][r.f], DYN ? rb[P][KK] + so : rb[P][KK]);
+        else xrd_tr<KK * 64 * BN + r.h * 8 * BN>(tb[D][r.f][r.h], DYN ? zb[P][r.f] + so : zb[P][r.f]);
       }
     };
-    // set S resident: wait for its reads; the k-major halves are joined
-    // only after the wait
-    auto xwait = [&](auto S_) __attribute__((always_inline)) {
-      constexpr int S = decltype(S_)::value;
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    // before MFMA idx of a step on set S: the fragments it is the first to use
+    // have landed; the k-major halves are joined only after the wait.
+    //   256x256: one wait for the whole set at the step's start, normally
+    //     already met (the reads had the last 16 MFMAs to land).
+    //   smaller tiles: LDS reads land in order and are issued in the order of
+    //     first use, so each first use waits until only the reads behind it
+    //     may be outstanding: this set's later ones and the q0(idx) reads of
+    //     the next set issued so far.  No scalar load may be in flight then (it
+    //     shares the counter): none is in the loop, and the loop is entered
+    //     with the counter at zero.
+    auto xwait = [&](auto S_, auto IDX_) __attribute__((always_inline)) {
+      constexpr int S = decltype(S_)::value, idx = decltype(IDX_)::value;
+      if constexpr (DYN) {
+        constexpr int i = idx / TN, j = idx % TN;
+        if constexpr (i == 0 || j == 0) {
+          // reads of this set up to the later of its first-used fragments
+          constexpr int pos = i > 0 ? TN * XRB + (i + 1) * XRA : (j + 1) * XRB + XRA;
+          constexpr int left = NRD - pos + x4_q0(idx, NRD, NM, S);
+          asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(left < 15 ? left : 15) : "memory");
+          if constexpr (!AK && j == 0) xfence(ta[S][i][0], ta[S][i][1]);
+          if constexpr (!BKC && i == 0) xfence(tb[S][j][0], tb[S][j][1]);
+        }
+      } else if constexpr (idx == 0) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (!AK) {
 #pragma unroll
-      for (int f = 0; f < 8; ++f) {
-        if constexpr (!AK) xfence(ta[S][f][0], ta[S][f][1]);
-        if constexpr (!BKC) xfence(tb[S][f][0], tb[S][f][1]);
+          for (int f = 0; f < TM; ++f) xfence(ta[S][f][0], ta[S][f][1]);
+        }
+        if constexpr (!BKC) {
+#pragma unroll
+          for (int f = 0; f < TN; ++f) xfence(tb[S][f][0], tb[S][f][1]);
+        }
       }
     };
     auto fragA = [&](auto S_, int i) __attribute__((always_inline)) {
@@ -525,93 +584,121 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
     };
     using Z0 = std::integral_constant<int, 0>;
     using Z1 = std::integral_constant<int, 1>;
-    // prologue: slices 0 and 1 in flight, slice 0 resident, its first
-    // k-step's fragments into set 0
+    // prologue: slices 0 .. NS-1 in flight (those past K fill their stage
+    // with zeros), slice 0 resident, its first k-step's fragments into set 0
     auto kv_of = [&](int kt) {
       const int64_t rem = K - (int64_t)kt * BK;
       return rem >= BK ? BK : rem > 0 ? (int)rem : 0;
     };
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl)
+    for (int sl = 0; sl < NS; ++sl) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        oa.load1(smem + sl * STAGE, (int64_t)sl * BK, kv_of(sl), t, wave, lane);
-        ob.load1(smem + sl * STAGE + OA::BYTES, (int64_t)sl * BK, kv_of(sl), t, wave, lane);
+      for (int t = 0; t < (OA::PERW > OB::PERW ? OA::PERW : OB::PERW); ++t) {
+        if (t < OA::PERW)
+          oa.load1(smem + sl * STAGE, (int64_t)sl * BK, kv_of(sl), t, wave, lane);
+        if (t < OB::PERW)
+          ob.load1(smem + sl * STAGE + OA::BYTES, (int64_t)sl * BK, kv_of(sl), t, wave, lane);
       }
-    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * PER_SLICE) : "memory");
     __syncthreads();
-    sfor<NRD>([&](auto Q) __attribute__((always_inline)) { xread(Q, Z0{}, Z0{}, Z0{}); });
-    const uint32_t mbase = __builtin_amdgcn_readfirstlane(sbase + wave * 8 * 1024);
+    sfor<NRD>([&](auto Q) __attribute__((always_inline)) { xread(Q, Z0{}, Z0{}, Z0{}, 0u); });
+    if constexpr (DYN) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const uint32_t mbase_a = __builtin_amdgcn_readfirstlane(sbase + wave * OA::PERW * 1024);
+    const uint32_t mbase_b = __builtin_amdgcn_readfirstlane(sbase + OA::BYTES + wave * OB::PERW * 1024);
     // One 32-wide k-step on set S; the next step's fragments come from
-    // stage P, k-step KK.  LD: 0 no loads, 1 loads of any slice at lk0 (lkv
-    // valid columns, masked) into the stage at lst, 2 loads of a full slice
-    // through the descriptors dA, dB into stage LP.
-    auto xstep = [&](auto S_, auto P_, auto KK_, auto LD_, char* lst, int64_t lk0, int lkv,
-                     auto LP_, u32x4 dA, u32x4 dB) __attribute__((always_inline)) {
+    // stage P (DYN: the stage at offset so), k-step KK.  LD: 0 no loads, 1
+    // loads of any slice at lk0 (lkv valid columns, masked), 2 loads of a full
+    // slice through the descriptors dA, dB; into stage LP (DYN: at offset lo).
+    auto xstep = [&](auto S_, auto P_, auto KK_, uint32_t so, auto LD_, int64_t lk0, int lkv, auto LP_,
+                     uint32_t lo, u32x4 dA, u32x4 dB) __attribute__((always_inline)) {
       constexpr int S = decltype(S_)::value;
       constexpr int LD = decltype(LD_)::value;
-      constexpr int LP = decltype(LP_)::value;
-      xwait(S_);
-      sfor<64>([&](auto IDX) __attribute__((always_inline)) {
+      constexpr int LO = DYN ? 0 : decltype(LP_)::value * STAGE;
+      sfor<NM>([&](auto IDX) __attribute__((always_inline)) {
         constexpr int idx = decltype(IDX)::value;
-        constexpr int i = idx / 8, j = idx % 8;
+        constexpr int i = idx / TN, j = idx % TN;
+        xwait(S_, IDX);
         xmma(acc[i][j], fragB(S_, j), fragA(S_, i));
-        // the slice barrier after the second step's first two MFMAs (they
-        // run on registers and cover the barrier's skew): slice kt+1
-        // resident for every wave, and nobody reads slice kt's stage any more
-        if constexpr (S == 1 && idx == 1) {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // the slice barrier after the second step's first MFMAs (they run on
+        // registers and cover the barrier's skew): slice kt+1 resident for
+        // every wave, and nobody reads slice kt's stage any more
+        if constexpr (S == 1 && idx == BAR) {
+          // (the stage's last reads, those of set 1, have landed here)
+          if constexpr (DYN)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * PER_SLICE) : "memory");
+          else
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * PER_SLICE) : "memory");
           __syncthreads();
         }
-        constexpr int q0 = x4_q0(idx, NRD), q1 = x4_q0(idx + 1, NRD);
-        static_assert(q1 - q0 <= 2, "at most two reads per MFMA");
-        sfor<2>([&](auto R_) __attribute__((always_inline)) {
-          constexpr int q = q0 + decltype(R_)::value;
-          if constexpr (q < q1) xread(std::integral_constant<int, q>{}, std::integral_constant<int, S ^ 1>{}, P_, KK_);
+        constexpr int q0 = x4_q0(idx, NRD, NM, S), q1 = idx == NM - 1 ? NRD : x4_q0(idx + 1, NRD, NM, S);
+        sfor<q1 - q0>([&](auto R_) __attribute__((always_inline)) {
+          xread(std::integral_constant<int, q0 + decltype(R_)::value>{}, std::integral_constant<int, S ^ 1>{}, P_,
+                KK_, so);
         });
-        if constexpr (LD == 1 && idx % 4 == 1) {
-          constexpr int t = idx / 4;
-          if constexpr (t < 8) oa.load1(lst, lk0, lkv, t, wave, lane);
-          else ob.load1(lst + OA::BYTES, lk0, lkv, t - 8, wave, lane);
-        }
-        if constexpr (LD == 2 && idx % 4 == 1) {
-          constexpr int t = idx / 4;
-          if constexpr (t < 8) dma16_at<LP * STAGE + t * 1024>(mbase, oa.voff[t], dA);
-          else dma16_at<LP * STAGE + OA::BYTES + (t - 8) * 1024>(mbase, ob.voff[t - 8], dB);
-        }
+        constexpr int l0 = x4_l0(idx, PER_SLICE, NM), l1 = x4_l0(idx + 1, PER_SLICE, NM);
+        if constexpr (LD != 0 && idx >= BAR)
+          sfor<l1 - l0>([&](auto T_) __attribute__((always_inline)) {
+            constexpr int t = l0 + decltype(T_)::value;
+            if constexpr (LD == 1) {
+              if constexpr (t < OA::PERW) oa.load1(smem + LO + lo, lk0, lkv, t, wave, lane);
+              else ob.load1(smem + LO + lo + OA::BYTES, lk0, lkv, t - OA::PERW, wave, lane);
+            } else {
+              if constexpr (t < OA::PERW)
+                dma16_at<LO + t * 1024>(DYN ? mbase_a + lo : mbase_a, oa.voff[t], dA);
+              else
+                dma16_at<LO + (t - OA::PERW) * 1024>(DYN ? mbase_b + lo : mbase_b, ob.voff[t - OA::PERW], dB);
+            }
+          });
       });
     };
     using NO = std::integral_constant<int, 0>;
     using YS = std::integral_constant<int, 1>;
     using FS = std::integral_constant<int, 2>;
     const u32x4 dz = {0, 0, 0, 0};
-    // Slices are taken in pairs (stage 0, stage 1).  For an odd slice count
-    // the last pair's second slice lies past K: its stage was filled with
-    // zeros, so its products add exact zeros (an accumulator that starts at
-    // +0 never holds -0), and the loop body has no branch.
-    auto xslice = [&](int kt, auto P_, auto FAST_) __attribute__((always_inline)) {
+    // slice kt in stage P (DYN: at offset so; the next slice's at sn): its two
+    // steps, and the loads of slice kt + NS into the stage it frees
+    auto xslice = [&](int kt, auto P_, uint32_t so, uint32_t sn, auto FAST_) __attribute__((always_inline)) {
       constexpr int P = decltype(P_)::value;
       constexpr bool FAST = decltype(FAST_)::value;
-      xstep(Z0{}, P_, Z1{}, NO{}, nullptr, 0, 0, P_, dz, dz);
-      const int64_t lk0 = (int64_t)(kt + 2) * BK;
+      xstep(Z0{}, P_, Z1{}, so, NO{}, 0, 0, P_, 0u, dz, dz);
+      const int64_t lk0 = (int64_t)(kt + NS) * BK;
       if constexpr (FAST)
-        xstep(Z1{}, std::integral_constant<int, P ^ 1>{}, Z0{}, FS{}, nullptr, 0, 0, P_,
-              oa.desc(lk0), ob.desc(lk0));
+        xstep(Z1{}, std::integral_constant<int, P ^ 1>{}, Z0{}, sn, FS{}, 0, 0, P_, so, oa.desc(lk0),
+              ob.desc(lk0));
       else
-        xstep(Z1{}, std::integral_constant<int, P ^ 1>{}, Z0{}, YS{}, smem + P * STAGE, lk0,
-              kv_of(kt + 2), P_, dz, dz);
+        xstep(Z1{}, std::integral_constant<int, P ^ 1>{}, Z0{}, sn, YS{}, lk0, kv_of(kt + NS), P_, so, dz, dz);
     };
-    // pairs whose loads (slices kt+2, kt+3) are whole slices inside K take
-    // the unmasked loads
+    // slices whose loads (slice kt + NS) are whole slices inside K take the
+    // unmasked loads
     const int nkf = (int)(K / BK);
     int kt = 0;
-    for (; kt + 3 < nkf; kt += 2) {
-      xslice(kt, Z0{}, std::true_type{});
-      xslice(kt + 1, Z1{}, std::true_type{});
-    }
-    for (; kt < nk; kt += 2) {
-      xslice(kt, Z0{}, std::false_type{});
-      xslice(kt + 1, Z1{}, std::false_type{});
+    if constexpr (DYN) {
+      uint32_t so = 0;
+      auto next = [&](uint32_t s_) { return s_ + STAGE == NS * STAGE ? 0u : s_ + STAGE; };
+      for (; kt + NS < nkf; ++kt) {
+        const uint32_t sn = next(so);
+        xslice(kt, Z0{}, so, sn, std::true_type{});
+        so = sn;
+      }
+      for (; kt < nk; ++kt) {
+        const uint32_t sn = next(so);
+        xslice(kt, Z0{}, so, sn, std::false_type{});
+        so = sn;
+      }
+    } else {
+      // Pairs of slices (stage 0, stage 1).  For an odd slice count the last
+      // pair's second slice lies past K: its stage was filled with zeros, so
+      // its products add exact zeros (an accumulator that starts at +0 never
+      // holds -0), and the loop body has no branch.
+      for (; kt + 3 < nkf; kt += 2) {
+        xslice(kt, Z0{}, 0u, 0u, std::true_type{});
+        xslice(kt + 1, Z1{}, 0u, 0u, std::true_type{});
+      }
+      for (; kt < nk; kt += 2) {
+        xslice(kt, Z0{}, 0u, 0u, std::false_type{});
+        xslice(kt + 1, Z1{}, 0u, 0u, std::false_type{});
+      }
     }
     // The last step read the fragments of a step that never runs: their
     // registers stay allocated until those reads have landed, so that no
@@ -620,18 +707,38 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
     // before the accumulators may be read sit in one statement that takes
     // every accumulator, so no spill or copy of one can be placed between
     // the last MFMA and the wait.
-#define X4_ROW(i) "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), \
-                  "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7])
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\t"
-                 "s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7"
-                 : X4_ROW(0), X4_ROW(1), X4_ROW(2), X4_ROW(3), X4_ROW(4), X4_ROW(5), X4_ROW(6), X4_ROW(7)
-                 :
-                 : "memory");
-#undef X4_ROW
+#define X4_W2(i) "+a"(acc[i][0]), "+a"(acc[i][1])
+#define X4_W4(i) X4_W2(i), "+a"(acc[i][2]), "+a"(acc[i][3])
+#define X4_W8(i) X4_W4(i), "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7])
+#define X4_END(...)                                                                       \
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\t"     \
+               "s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7"                                 \
+               : __VA_ARGS__                                                              \
+               :                                                                          \
+               : "memory")
+    if constexpr (TM == 8 && TN == 8)
+      X4_END(X4_W8(0), X4_W8(1), X4_W8(2), X4_W8(3), X4_W8(4), X4_W8(5), X4_W8(6), X4_W8(7));
+    else if constexpr (TM == 8 && TN == 4)
+      X4_END(X4_W4(0), X4_W4(1), X4_W4(2), X4_W4(3), X4_W4(4), X4_W4(5), X4_W4(6), X4_W4(7));
+    else if constexpr (TM == 4 && TN == 8)
+      X4_END(X4_W8(0), X4_W8(1), X4_W8(2), X4_W8(3));
+    else if constexpr (TM == 4 && TN == 4)
+      X4_END(X4_W4(0), X4_W4(1), X4_W4(2), X4_W4(3));
+    else {
+      static_assert(TM == 2 && TN == 2, "wave tiles of the 4-wave loop");
+      X4_END(X4_W2(0), X4_W2(1));
+    }
+#undef X4_W2
+#undef X4_W4
+#undef X4_W8
+#undef X4_END
 #pragma unroll
-    for (int f = 0; f < 8; ++f) {
+    for (int f = 0; f < TM; ++f) {
       if constexpr (AK) xkeep(xa[0][f]);
       else xkeep(ta[0][f][0], ta[0][f][1]);
+    }
+#pragma unroll
+    for (int f = 0; f < TN; ++f) {
       if constexpr (BKC) xkeep(xb[0][f]);
       else xkeep(tb[0][f][0], tb[0][f][1]);
     }
@@ -925,13 +1032,6 @@ template <int BM, int BN, int WGM, int WGN, int BK, int NS, bool TA, bool TB, in
 hipError_t launch(const GemmArgs& g, hipStream_t s, int splits = 1) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = EPI == 1 ? (int)((g.F + BN / 2 - 1) / (BN / 2)) : (int)((g.N + BN - 1) / BN);
-  if constexpr (BM == 256 && BN == 256 && WGM == 2 && WGN == 4 && EPI <= 3 && !RK && BK == 64 && NS == 2) {
-    hipLaunchKernelGGL((gemm_f16_kernel<256, 256, 2, 2, 64, 2, TA, TB, EPI, false>),
-                       dim3(tiles_m * tiles_n, splits), dim3(4 * kWave), 0, s, g.M, g.N, g.K, g.alpha,
-                       g.A, g.lda, g.B, g.ldb, g.beta, g.R, g.ldr, g.C, g.ldc, tiles_m, tiles_n, 8,
-                       g.X1, g.ldx1, g.F, g.pair_off > 0 ? g.pair_off : g.F, g.bias);
-    return hipGetLastError();
-  }
   hipLaunchKernelGGL((gemm_f16_kernel<BM, BN, WGM, WGN, BK, NS, TA, TB, EPI, RK>),
                      dim3(tiles_m * tiles_n, splits), dim3(WGM * WGN * kWave), 0, s, g.M, g.N, g.K, g.alpha,
                      g.A, g.lda, g.B, g.ldb, g.beta, g.R, g.ldr, g.C, g.ldc, tiles_m, tiles_n, 8,
@@ -1015,85 +1115,71 @@ splitk_reduce_kernel(const float* __restrict__ W, int S, int64_t Mt, int64_t Nt,
   *reinterpret_cast<half8*>(C + m * ldc + n) = o;
 }
 
+// one launch of one tile size; LDS stages as many as fit 160 KiB
+template <bool TA, bool TB, int EPI>
+hipError_t launch_tile(int tile, const GemmArgs& g, hipStream_t s) {
+  switch (tile) {
+    case kTile256: return launch<256, 256, 2, 2, 64, 2, TA, TB, EPI>(g, s);
+    case kTile256x128: return launch<256, 128, 2, 2, 64, 3, TA, TB, EPI>(g, s);
+    case kTile128x256: return launch<128, 256, 2, 2, 64, 3, TA, TB, EPI>(g, s);
+    case kTile128: return launch<128, 128, 2, 2, 64, 4, TA, TB, EPI>(g, s);
+    default: return launch<64, 64, 2, 2, 64, 8, TA, TB, EPI>(g, s);
+  }
+}
+
 template <bool TA, bool TB, int EPI>
 hipError_t dispatch_tile(const GemmArgs& g, hipStream_t s) {
-  // 256x256 tiles once there are about as many tiles as CUs; smaller
-  // problems use 128x128 tiles so that more workgroups exist.
-  const int64_t unit_n = EPI == 1 ? 128 : 256;            // output columns per 256-wide tile
-  const int64_t ncols = EPI == 1 ? g.F : g.N;
-  const int64_t tm = (g.M + 255) / 256, tn = (ncols + unit_n - 1) / unit_n;
-  const int64_t big_tiles = tm * tn;
-  // A last wave at most half full runs as half-size tiles in one short round:
-  // whole waves of 256x256 tiles first, then the remaining columns (or rows)
-  // as 256x128 (or 128x256) tiles.
-  constexpr int64_t kCUs = 256;
-  const int64_t waves = big_tiles / kCUs, rem = big_tiles % kCUs;
-  SplitTail st;
-  if constexpr (EPI == 0) {
-    // K not a multiple of 8 (no layer shape): one launch of the tiles with
-    // the last slice's fix-up (256x256 from about one wave of them)
+  if constexpr (EPI == 0 && (!TA || TB)) {
+    // K not a multiple of 8 with a K-contiguous operand: one launch of the
+    // tiles with the last slice's fix-up (256x256 from about one wave of
+    // them).  Weight gradients (both operands k-major) load whole k-rows and
+    // need no fix-up.
     if (g.K & 7) {
-      if (big_tiles >= 192) return launch<256, 256, 2, 4, 64, 2, TA, TB, 0, true>(g, s);
+      if (((g.M + 255) / 256) * ((g.N + 255) / 256) >= 192)
+        return launch<256, 256, 2, 4, 64, 2, TA, TB, 0, true>(g, s);
       return launch<128, 128, 2, 2, 64, 2, TA, TB, 0, true>(g, s);
     }
-    if (g.ws != nullptr && gemm_splitk_tail(g.M, g.N, g.K, &st) &&
-        gemm_splitk_ws_bytes(g.M, g.N, g.K) <= g.ws_bytes) {
-      // The last wave (or a launch of less than one wave) as split-K 256x256
-      // tiles: whole waves first (full K), then the remaining tiles' K split
-      // S ways (FP32 partials in the workspace), then the fixed-order sum
-      // with alpha, beta * R and bias.
-      GemmArgs head = g, tail;
-      if (st.columns) {
-        head.N = st.split_at;
-        tail = column_part<TA, TB, 0>(g, st.split_at);
+  }
+  const bool split_k = EPI == 0 && g.ws != nullptr && gemm_splitk_ws_bytes(g.M, g.N, g.K) <= g.ws_bytes;
+  const GemmPlan p = gemm_plan(TA, g.M, EPI == 1 ? g.F : g.N, g.K, EPI, EPI == 0 && g.beta != 0.f, split_k);
+  GemmArgs tail = g;
+  if (p.split_at > 0) {
+    GemmArgs head = g;
+    if (!p.columns) {
+      head.M = p.split_at;
+      tail = row_part<TA, TB, EPI>(g, p.split_at);
+    } else {
+      if (EPI == 1) {
+        head.pair_off = g.pair_off > 0 ? g.pair_off : g.F;
+        head.F = p.split_at;
+        head.N = 2 * p.split_at;
       } else {
-        head.M = st.split_at;
-        tail = row_part<TA, TB, 0>(g, st.split_at);
+        head.N = p.split_at;
       }
-      hipError_t e = hipSuccess;
-      if (st.split_at > 0) e = launch<256, 256, 2, 4, 64, 2, TA, TB, 0>(head, s);
-      if (e != hipSuccess) return e;
+      tail = column_part<TA, TB, EPI>(g, p.split_at);
+    }
+    const hipError_t e = launch_tile<TA, TB, EPI>(p.head, head, s);
+    if (e != hipSuccess) return e;
+  }
+  if constexpr (EPI == 0) {
+    if (p.splits > 1) {
+      // the tail's K split over p.splits workgroups per tile (FP32 partials in
+      // the workspace), then the fixed-order sum with alpha, beta * R and bias
       GemmArgs part = tail;
       part.C = reinterpret_cast<lt_half*>(g.ws);
-      part.ldc = st.Nt;
+      part.ldc = tail.N;
       part.beta = 0.f;
       part.bias = nullptr;
-      e = launch<256, 256, 2, 4, 64, 2, TA, TB, 3>(part, s, st.S);
+      const hipError_t e = launch<256, 256, 2, 2, 64, 2, TA, TB, 3>(part, s, p.splits);
       if (e != hipSuccess) return e;
-      const int64_t threads = st.Mt * (st.Nt / 8);
+      const int64_t threads = tail.M * (tail.N / 8);
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0,
-                         s, g.ws, st.S, st.Mt, st.Nt, g.alpha, g.beta, tail.R, tail.ldr, tail.bias,
+                         s, g.ws, p.splits, tail.M, tail.N, g.alpha, g.beta, tail.R, tail.ldr, tail.bias,
                          tail.C, tail.ldc);
       return hipGetLastError();
     }
   }
-  if (big_tiles < 192) return launch<128, 128, 2, 2, 64, 2, TA, TB, EPI>(g, s);
-  if (waves >= 1 && rem > 0 && 2 * rem <= kCUs) {
-    const int64_t full = waves * kCUs;
-    if (full % tm == 0 && full / tm < tn) {
-      const int64_t n_main = (full / tm) * unit_n;
-      GemmArgs head = g;
-      if (EPI == 1) {
-        head.pair_off = g.pair_off > 0 ? g.pair_off : g.F;
-        head.F = n_main;
-        head.N = 2 * n_main;
-      } else {
-        head.N = n_main;
-      }
-      hipError_t e = launch<256, 256, 2, 4, 64, 2, TA, TB, EPI>(head, s);
-      if (e != hipSuccess) return e;
-      return launch<256, 128, 4, 2, 64, 2, TA, TB, EPI>(column_part<TA, TB, EPI>(g, n_main), s);
-    }
-    if (full % tn == 0 && full / tn < tm) {
-      const int64_t m_main = (full / tn) * 256;
-      GemmArgs head = g;
-      head.M = m_main;
-      hipError_t e = launch<256, 256, 2, 4, 64, 2, TA, TB, EPI>(head, s);
-      if (e != hipSuccess) return e;
-      return launch<128, 256, 2, 4, 64, 2, TA, TB, EPI>(row_part<TA, TB, EPI>(g, m_main), s);
-    }
-  }
-  return launch<256, 256, 2, 4, 64, 2, TA, TB, EPI>(g, s);
+  return launch_tile<TA, TB, EPI>(p.tail, tail, s);
 }
 
 }  // namespace

@@ -54,6 +54,27 @@ bool gemm_splitk_tail(int64_t M, int64_t N, int64_t K, SplitTail* p);
 // FP32 workspace bytes the split needs (0 when gemm_splitk_tail is false)
 size_t gemm_splitk_ws_bytes(int64_t M, int64_t N, int64_t K);
 
+// Output tiles of the GEMM kernels, largest first.
+enum GemmTile { kTile256 = 0, kTile256x128, kTile128x256, kTile128, kTile64, kNumGemmTiles };
+struct GemmTileDim {
+  int m, n;
+};
+constexpr GemmTileDim kGemmTileDim[kNumGemmTiles] = {{256, 256}, {256, 128}, {128, 256}, {128, 128}, {64, 64}};
+
+// How one GEMM call is launched: its first split_at columns (or rows) as
+// `head` tiles, the rest as `tail` tiles; splits > 1: the tail as 256x256
+// tiles with K split over that many workgroups (FP32 partials in the
+// workspace) and a fixed-order sum.  split_at = 0: the tail is everything.
+struct GemmPlan {
+  bool columns;
+  int64_t split_at;
+  int head, tail;
+  int splits;
+};
+// N in output columns (gate columns for epilogue 1); split_k: the caller's
+// workspace holds gemm_splitk_ws_bytes(M, N, K).
+GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k);
+
 struct AttnShape {
   int B, S, Hq, Hkv, D;
   float scale;

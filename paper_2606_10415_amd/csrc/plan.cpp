@@ -6,6 +6,8 @@
 
 namespace lt {
 
+// The split a workspace is sized for; whether a call with a workspace takes
+// it is decided by gemm_plan below.
 bool gemm_splitk_tail(int64_t M, int64_t N, int64_t K, SplitTail* p) {
   // the geometry of the half-tile tail (256x256 tiles, one wave = 256 CUs),
   // with the last wave's K split so that its units fill about one wave; a
@@ -64,6 +66,102 @@ size_t gemm_splitk_ws_bytes(int64_t M, int64_t N, int64_t K) {
   SplitTail p;
   if (!gemm_splitk_tail(M, N, K, &p)) return 0;
   return (size_t)p.S * (size_t)p.Mt * (size_t)p.Nt * sizeof(float);
+}
+
+namespace {
+
+constexpr int64_t kPlanCUs = 256;
+// Time of one 64-wide K-slice of a tile (us): with few CUs busy, and what a
+// full chip adds (power lowers the clock, and the operand loads share L2 and
+// the memory-side cache); of the rest of a round of tiles (prologue, epilogue
+// and its memory traffic), for the plain, gate/up and SwiGLU-gradient
+// epilogues; and of reading R in the plain one.  From 4096-row GEMMs at K =
+// 4096 and 8192 on random operands (slope and intercept): 256x256 tiles
+// 107 / 197 us in one round, 256x128 120 / 227 in two, 128x128 136 / 262 in
+// four, 64x64 240 / 425 in sixteen.
+struct TileCost {
+  double slice, load, slice_tn, load_tn, fixed[3], r;
+};
+constexpr TileCost kTileCost[kNumGemmTiles] = {
+    {0.90, 0.50, 0.90, 0.52, {12.0, 20.0, 35.0}, 8.0},
+    {0.57, 0.26, 0.60, 0.29, {5.5, 10.0, 18.0}, 4.0},
+    {0.57, 0.27, 0.60, 0.30, {5.5, 10.0, 18.0}, 4.0},
+    {0.36, 0.12, 0.38, 0.14, {3.0, 9.0, 14.0}, 2.0},
+    {0.16, 0.02, 0.20, 0.03, {2.5, 7.0, 11.0}, 0.5},
+};
+constexpr double kLaunchUs = 4.0;            // a further launch in the stream
+constexpr double kPartialBytesPerUs = 4.5e6;  // split-K partials: written, then read
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// us of `tiles` tiles of a kind, nk K-slices each
+double tiles_cost(int tile, bool tn, int epi, bool reads_r, int64_t tiles, int64_t nk) {
+  const TileCost& c = kTileCost[tile];
+  auto round = [&](int64_t n) {
+    const double x = (double)n / kPlanCUs;
+    const double busy = tile == kTile256 ? x : x * x;
+    return (double)nk * ((tn ? c.slice_tn : c.slice) + (tn ? c.load_tn : c.load) * busy) + c.fixed[epi] +
+           (reads_r ? c.r : 0.0);
+  };
+  const int64_t full = tiles / kPlanCUs, rem = tiles % kPlanCUs;
+  return (double)full * round(kPlanCUs) + (rem ? round(rem) : 0.0);
+}
+
+// ... of an M x N region
+double region_cost(int tile, bool tn, int epi, bool reads_r, int64_t M, int64_t N, int64_t nk) {
+  const int64_t bn = epi == 1 ? kGemmTileDim[tile].n / 2 : kGemmTileDim[tile].n;
+  return tiles_cost(tile, tn, epi, reads_r, ceil_div(M, kGemmTileDim[tile].m) * ceil_div(N, bn), nk);
+}
+
+}  // namespace
+
+// The launch with the least estimated time among
+//   * one launch of one tile size;
+//   * r whole rounds of 256x256 tiles (one tile per CU and round), the
+//     remaining columns or rows as tiles of any size -- a last round that a
+//     large tile would leave half empty;
+//   * the split-K plan, given a workspace: whole rounds, then the remaining
+//     tiles with K split; it pays where few tiles face a long K.
+// Larger tiles cost less per FLOP (the 256x256 tile's slice: 1.40 us, four
+// 128x128 slices: 1.92 us), smaller ones fill the CUs and their last round.
+GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k) {
+  const bool tn = transA != 0;
+  const int64_t nk = ceil_div(K, 64);
+  GemmPlan best{true, 0, kTile256, kTile256, 1};
+  double best_us = 1e30;
+  auto offer = [&](const GemmPlan& p, double us) {
+    if (us < best_us) {
+      best = p;
+      best_us = us;
+    }
+  };
+  for (int t = 0; t < kNumGemmTiles; ++t)
+    offer(GemmPlan{true, 0, t, t, 1}, region_cost(t, tn, epi, reads_r, M, N, nk));
+  const int64_t un = epi == 1 ? 128 : 256;         // output columns per 256-wide tile
+  const int64_t tm = ceil_div(M, 256), tc = ceil_div(N, un);
+  for (int cols = 0; cols < 2; ++cols) {
+    const int64_t across = cols ? tm : tc;         // tiles per tile column (row)
+    const int64_t along = cols ? tc : tm;
+    const int64_t rounds = tm * tc / kPlanCUs;
+    if (rounds < 1 || across > kPlanCUs) continue;
+    const int64_t n = rounds * kPlanCUs / across;  // tile columns (rows) in whole rounds
+    if (n < 1 || n >= along) continue;
+    const double head = tiles_cost(kTile256, tn, epi, reads_r, n * across, nk);
+    const int64_t at = n * (cols ? un : 256);
+    for (int t = 0; t < kNumGemmTiles; ++t)
+      offer(GemmPlan{cols == 1, at, kTile256, t, 1},
+            head + kLaunchUs + region_cost(t, tn, epi, reads_r, cols ? M : M - at, cols ? N - at : N, nk));
+  }
+  SplitTail st;
+  if (split_k && epi == 0 && gemm_splitk_tail(M, N, K, &st)) {
+    const int64_t tail = ceil_div(st.Mt, 256) * ceil_div(st.Nt, 256);
+    const int64_t rest = tm * tc - tail;
+    const double sum = 2.0 * 4.0 * st.S * (double)st.Mt * (double)st.Nt / kPartialBytesPerUs;
+    offer(GemmPlan{st.columns, st.split_at, kTile256, kTile256, st.S},
+          tiles_cost(kTile256, tn, 0, reads_r, rest, nk) + (rest ? kLaunchUs : 0.0) +
+              tiles_cost(kTile256, tn, 0, false, tail * st.S, ceil_div(nk, st.S)) + kLaunchUs + sum);
+  }
+  return best;
 }
 
 }  // namespace lt

@@ -1,0 +1,112 @@
+"""Launch plans of the GEMM: which tiles a call runs as (host code), and the tiles on the GPU.
+
+CPU: the plan's regions cover the output once, on tile boundaries, for random
+sizes, epilogues and layouts; split-K plans only where the workspace rule has one.
+GPU: one shape per kind of plan and layout (ragged rows, columns and K among
+them) with integer operands, whose FP32 sums are exact, so the result equals the
+float64 product bit for bit.
+"""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_10415_amd.synth import uniform_int_f16
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = "/opt/rocm"
+
+PROGRAM = r"""
+#include "../paper_2606_10415_amd/csrc/kernels.hpp"
+#include <cstdio>
+#include <random>
+using namespace lt;
+int main() {
+  std::mt19937_64 r(1);
+  long bad = 0, n = 0, kinds[kNumGemmTiles] = {}, split = 0, two = 0;
+  auto size = [&](int hi) { return (int64_t)1 << (r() % hi); };
+  for (int it = 0; it < 200000; ++it) {
+    const int64_t M = 1 + r() % (size(15)), N = 1 + r() % (size(16)), K = 1 + r() % (size(15));
+    const int tA = r() % 2, epi = tA ? 0 : (int)(r() % 3);
+    const bool ws = r() % 2, rd = epi == 0 && r() % 2;
+    const GemmPlan p = gemm_plan(tA, M, N, K, epi, rd, ws);
+    ++n;
+    bool ok = p.tail >= 0 && p.tail < kNumGemmTiles && p.split_at >= 0 && p.splits >= 1;
+    const int64_t unit = p.columns ? (epi == 1 ? 128 : 256) : 256;
+    if (p.split_at) ok = ok && p.head == kTile256 && p.split_at % unit == 0 && p.split_at < (p.columns ? N : M);
+    SplitTail st;
+    if (p.splits > 1)
+      ok = ok && ws && epi == 0 && p.tail == kTile256 && gemm_splitk_tail(M, N, K, &st) && st.S == p.splits &&
+           st.split_at == p.split_at && (!p.split_at || st.columns == p.columns);
+    bad += !ok;
+    ++kinds[p.tail];
+    split += p.splits > 1;
+    two += p.split_at > 0;
+  }
+  // the largest sizes the entry points accept
+  for (int tA = 0; tA < 2; ++tA) {
+    const GemmPlan p = gemm_plan(tA, (int64_t)1 << 30, (int64_t)1 << 30, (int64_t)1 << 30, 0, true, true);
+    bad += p.tail != kTile256 || p.splits != 1;
+  }
+  bool all = split && two;
+  for (int t = 0; t < kNumGemmTiles; ++t) all = all && kinds[t] > 0;
+  std::printf("%ld plans, %ld bad, every kind %d\n", n, bad, (int)all);
+  return bad || !all;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(f"{ROCM}/include/hip"),
+                    reason="needs g++ and the HIP headers")
+def test_plans_cover_the_output(tmp_path):
+    src, exe = tmp_path / "plan_check.cpp", tmp_path / "plan_check"
+    src.write_text(PROGRAM.replace("../paper_2606_10415_amd", f"{ROOT}/paper_2606_10415_amd"))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{ROOT}/include", str(src),
+                    os.path.join(ROOT, "paper_2606_10415_amd", "csrc", "plan.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr[-2000:]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transA,transB", [(0, 1), (0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,ws", [
+    (65, 72, 64, False),        # 64x64 tiles, one slice in the eight-stage ring
+    (200, 328, 584, False),     # 64x64, more slices than stages, last slice 8 wide
+    (1000, 4096, 328, False),   # 128x128
+    (1237, 5120, 456, False),   # two-launch and 256x128 plans, ragged rows
+    (2048, 4096, 1224, False),  # 256x128 or 128x256, one round
+    (1237, 7168, 200, True),    # workspace given, not taken
+    (1104, 4120, 1237, False),  # K odd: whole k-rows for weight gradients, fix-up elsewhere
+])
+def test_plan_tiles_exact_integers(transA, transB, M, N, K, ws):
+    import torch
+    from paper_2606_10415_amd import lt
+
+    print(f"gemm plan trans=({transA},{transB}) M={M} N={N} K={K} ws={ws}", flush=True)
+    a, b = uniform_int_f16(41, (M, K), -2, 2), uniform_int_f16(42, (K, N), -2, 2)
+    r = uniform_int_f16(43, (M, N), -8, 8)
+
+    def stored(x, trans):
+        st = np.ascontiguousarray(x.T if trans else x)
+        out = np.full((st.shape[0], -(-st.shape[1] // 8) * 8), np.nan, np.float16)   # padding is never used
+        out[:, :st.shape[1]] = st
+        return torch.from_numpy(out).cuda()
+
+    A, B, R = stored(a, transA), stored(b, transB), torch.from_numpy(r).cuda()
+    C = torch.full((M + 1, N), 777.0, dtype=torch.float16, device="cuda")           # a guard row
+    if ws:
+        need = max(lt.lt_gemm_f16_workspace_size(transA, transB, M, N, K), 16)
+        w = torch.empty(need, dtype=torch.uint8, device="cuda")
+        lt.lt_gemm_f16_ws(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, N, None, C, N, w, need)
+    else:
+        lt.lt_gemm_f16_res(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, N, C, N)
+    got = C.cpu().numpy()
+    rows = np.unique(np.concatenate([np.random.default_rng(0).choice(M, min(M, 96), replace=False), [0, M - 1]]))
+    ref = oracle.gemm(0, 0, 3.0, a[rows], b, -2.0, r[rows]).astype(np.float16)
+    assert np.array_equal(got[rows].view(np.uint16), ref.view(np.uint16))
+    assert (got[M] == 777.0).all()
