@@ -71,26 +71,28 @@ size_t gemm_splitk_ws_bytes(int64_t M, int64_t N, int64_t K) {
 namespace {
 
 constexpr int64_t kPlanCUs = 256;
-// Time of one 64-wide K-slice of a tile (us): with few CUs busy, and what a
-// full chip adds (power lowers the clock, and the operand loads share L2 and
-// the memory-side cache); of the rest of a round of tiles (prologue, epilogue
-// and its memory traffic), for the plain, gate/up and SwiGLU-gradient
-// epilogues; and of reading R in the plain one.  From 4096-row GEMMs at K =
-// 4096 and 8192 on random operands (slope and intercept): 256x256 tiles
-// 107 / 197 us in one round, 256x128 120 / 227 in two, 128x128 136 / 262 in
-// four, 64x64 240 / 425 in sixteen.
+// Time of one 64-wide K-slice of a tile (us; NT / NN and TN layouts), what it
+// adds with every CU busy (power lowers the clock, operand loads share L2 and
+// the memory-side cache), and the rest of a round of tiles (prologue,
+// epilogue and its memory traffic) for the plain, gate/up and SwiGLU-gradient
+// epilogues and, in the plain one, for reading R.  Fitted to calls whose
+// operands come from HBM, as a program's weights and activations do (calls
+// on cached operands run 10-25% faster, the smaller tiles most): 1024 x 4096 x
+// {4096, 11008} NT take 103 / 264 us as 256x256 tiles, 59.5 / 156 as 256x128,
+// 42 / 111 as 128x128, 77 / 195 as 64x64; 4096 x 4096 x {4096, 11008} 112 / 286,
+// 124 / 317, 155 / 417, 296 / 749.
 struct TileCost {
-  double slice, load, slice_tn, load_tn, fixed[3], r;
+  double slice, slice_tn, load, fixed[3], r;
 };
 constexpr TileCost kTileCost[kNumGemmTiles] = {
-    {0.90, 0.50, 0.90, 0.52, {12.0, 20.0, 35.0}, 8.0},
-    {0.57, 0.26, 0.60, 0.29, {5.5, 10.0, 18.0}, 4.0},
-    {0.57, 0.27, 0.60, 0.30, {5.5, 10.0, 18.0}, 4.0},
-    {0.36, 0.12, 0.38, 0.14, {3.0, 9.0, 14.0}, 2.0},
-    {0.16, 0.02, 0.20, 0.03, {2.5, 7.0, 11.0}, 0.5},
+    {1.46, 1.33, 0.10, {8.0, 10.0, 28.0}, 8.0},
+    {0.87, 0.91, 0.03, {4.0, 5.0, 16.0}, 4.0},
+    {0.88, 0.92, 0.03, {4.0, 5.0, 16.0}, 4.0},
+    {0.50, 0.52, 0.10, {1.5, 2.0, 9.0}, 2.0},
+    {0.25, 0.26, 0.02, {1.5, 3.0, 7.0}, 0.5},
 };
-constexpr double kLaunchUs = 4.0;            // a further launch in the stream
-constexpr double kPartialBytesPerUs = 4.5e6;  // split-K partials: written, then read
+constexpr double kLaunchUs = 4.0;             // a further launch in the stream
+constexpr double kPartialBytesPerUs = 9.0e6;  // split-K partials, written, then read
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -98,9 +100,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 double tiles_cost(int tile, bool tn, int epi, bool reads_r, int64_t tiles, int64_t nk) {
   const TileCost& c = kTileCost[tile];
   auto round = [&](int64_t n) {
-    const double x = (double)n / kPlanCUs;
-    const double busy = tile == kTile256 ? x : x * x;
-    return (double)nk * ((tn ? c.slice_tn : c.slice) + (tn ? c.load_tn : c.load) * busy) + c.fixed[epi] +
+    return (double)nk * ((tn ? c.slice_tn : c.slice) + c.load * (double)n / kPlanCUs) + c.fixed[epi] +
            (reads_r ? c.r : 0.0);
   };
   const int64_t full = tiles / kPlanCUs, rem = tiles % kPlanCUs;
@@ -122,8 +122,8 @@ double region_cost(int tile, bool tn, int epi, bool reads_r, int64_t M, int64_t 
 //     large tile would leave half empty;
 //   * the split-K plan, given a workspace: whole rounds, then the remaining
 //     tiles with K split; it pays where few tiles face a long K.
-// Larger tiles cost less per FLOP (the 256x256 tile's slice: 1.40 us, four
-// 128x128 slices: 1.92 us), smaller ones fill the CUs and their last round.
+// Larger tiles cost less per FLOP (the 256x256 tile's slice: 1.56 us, four
+// 128x128 slices: 2.4 us), smaller ones fill the CUs and their last round.
 GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k) {
   const bool tn = transA != 0;
   const int64_t nk = ceil_div(K, 64);
