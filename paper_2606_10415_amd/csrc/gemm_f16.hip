@@ -873,157 +873,169 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
               make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
       }
     }
-  } else if constexpr (EPI == 1) {
-    // accumulator blocks j and j + TN/2 hold the gate and up columns of the
-    // same n: GU[m][n] = G, GU[m][F + n] = U, A[m][n] = silu(G) U (from the
-    // FP32 values, one rounding each)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int64_t m = m0 + wm * WTM + i * 16 + (lane & 15);
-      if (m >= M) continue;
-#pragma unroll
-      for (int j = 0; j < TN / 2; ++j) {
-        const int64_t n = n0 + wn * (WTN / 2) + j * 16 + 4 * (lane >> 4);
-        if (n >= Fb) continue;
-        half4 g4, u4, a4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float g = alpha * acc[i][j][e];
-          const float u = alpha * acc[i][j + TN / 2][e];
-          g4[e] = (_Float16)g;
-          u4[e] = (_Float16)u;
-          a4[e] = (_Float16)(g * sigmoid_f(g) * u);
-        }
-        *reinterpret_cast<half4*>(C + m * ldc + n) = g4;
-        *reinterpret_cast<half4*>(C + m * ldc + P + n) = u4;
-        *reinterpret_cast<half4*>(X1 + m * ldx1 + n) = a4;
-      }
-    }
   } else {
-    // The rows of the wave tile are handled in NG groups: the loads of group
-    // g (beta * R, or G and U for the SwiGLU gradient) are issued before the
-    // stores of group g - 1, and group g's values are computed only after
-    // those stores are in flight.  Loads and stores share one completion
-    // counter, so a load consumed after a store is waited for together with
-    // that store: in this order every group costs one overlapped memory
-    // round trip instead of one per 16x16 block.  R may be C itself; groups
-    // touch disjoint rows, so loading group g before storing group g - 1 is
-    // safe.
-    constexpr int NL = EPI == 2 ? 2 : 1;               // half4 per block and lane, in and out
-    constexpr int NG = EPI == 2 ? (TM >= 4 ? 4 : TM) : (TM >= 2 ? 2 : 1);
-    constexpr int IG = TM / NG;                        // accumulator rows per group
-    static_assert(TM % NG == 0, "row groups");
-    const bool reads = EPI == 2 || beta != 0.f;        // uniform over the grid
-    const int64_t mb = m0 + wm * WTM + (lane & 15);
-    const int64_t nb = n0 + wn * WTN + 4 * (lane >> 4);
-    half4 in[IG][TN][NL];
-    half4 out[IG][TN][NL];
-    // bias (epilogue 0): the same 4 columns for every accumulator row
-    const bool has_bias = EPI == 0 && bias != nullptr;   // uniform over the grid
-    half4 bv[TN];
+    // Each wave passes its accumulators through LDS, 16 rows at a time (FP32,
+    // wave-private, rows 16 bytes apart in the banks), so that a lane gets
+    // 8 consecutive columns of one row: R, G, U and bias are then read and
+    // results written 16 bytes per lane, whole 128-byte lines per row.  In
+    // the accumulator layout a store instruction touched 16 rows with 32
+    // bytes each.
+    constexpr int NC = EPI == 1 ? WTN / 2 : WTN;       // output columns of the wave
+    constexpr int CH = NC / 8;                         // 8-column chunks per row
+    constexpr int RPP = 64 / CH < 16 ? 64 / CH : 16;   // rows per pass over the lanes
+    constexpr int NPASS = 16 / RPP;
+    constexpr int PITCH = WTN + 4;                     // floats per staged row
+    constexpr int NL = EPI == 2 ? 2 : 1;               // 16-byte reads per chunk
+    constexpr int PF = TM < 3 ? TM : 3;                // row groups of reads in flight
+    static_assert(NWAVE * 16 * PITCH * 4 <= NS * STAGE, "staging fits in LDS");
+    const bool reads = EPI == 2 || (EPI == 0 && beta != 0.f);   // uniform over the grid
+    const bool has_bias = EPI == 0 && bias != nullptr;
+    const int64_t ncols = EPI == 1 ? Fb : N;
+    const int crow = lane / CH, ccol = 8 * (lane % CH);
+    const bool lane_on = 64 / CH <= 16 || crow < 16;   // 16-column tiles: half the lanes
+    const int64_t mb = m0 + wm * WTM + crow;
+    const int64_t n = n0 + wn * NC + ccol;
+    // loads still in flight (the slices past K) and other waves' last reads
+    // of the stages come first
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    float* stg = reinterpret_cast<float*>(smem) + wave * (16 * PITCH);
+    float* const wr = stg + (lane & 15) * PITCH + 4 * (lane >> 4);
+    const float* const rd = stg + (lane_on ? crow : 0) * PITCH + ccol;
+    half8 bv;
     if (has_bias) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int64_t n = nb + j * 16;
-        if (n + 4 <= N) {
-          bv[j] = *reinterpret_cast<const half4*>(bias + n);
-        } else {
-          // bias holds exactly N entries
+      for (int e = 0; e < 8; ++e) bv[e] = (_Float16)0;
+      if (n + 8 <= N) {
+        bv = as_half8(ld16(bias + n));
+      } else {
+        // bias holds exactly N entries
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            bv[j][e] = n + e < N ? __builtin_bit_cast(_Float16, bias[n + e]) : (_Float16)0;
-        }
+        for (int e = 0; e < 8; ++e)
+          if (n + e < N) bv[e] = __builtin_bit_cast(_Float16, bias[n + e]);
       }
     }
-
-    // loads are unconditional, from addresses clamped into the matrix
-    // (values of out-of-range blocks are never stored): no branch between
-    // the loads keeps the completion-counter waits exact
-    auto load_group = [&](int g) {
+    // FULL: the whole tile lies inside the matrix -- no branch between the
+    // loads and stores, which keeps the completion-counter waits exact.
+    // Otherwise loads come from addresses clamped into the matrix (values of
+    // out-of-range chunks are never stored; a chunk that starts before N is
+    // read whole: rows are readable up to N rounded up to 8, as leading
+    // dimensions are multiples of 8).  R may be C itself: every row group is
+    // read before any group from it on is stored.
+    auto finish = [&](auto FULL_) __attribute__((always_inline)) {
+      constexpr bool FULL = decltype(FULL_)::value;
+      half8 in[PF][NPASS][NL];
+      auto load_group = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-      for (int ii = 0; ii < IG; ++ii) {
-        const int64_t m = mb + (g * IG + ii) * 16;
-        const int64_t mc = m < M ? m : M - 1;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          // a 4-column group that starts before N is read whole: rows are
-          // readable up to N rounded up to 8 (leading dimensions are
-          // multiples of 8)
-          const int64_t n = nb + j * 16;
-          const int64_t nc = n < N ? n : 0;
+        for (int p = 0; p < NPASS; ++p) {
+          const int64_t m = mb + i * 16 + p * RPP;
+          const int64_t mc = FULL || m < M ? m : M - 1;
+          const int64_t nc = FULL || n < N ? n : 0;
           if constexpr (EPI == 2) {
-            in[ii][j][0] = *reinterpret_cast<const half4*>(X1 + mc * ldx1 + nc);
-            in[ii][j][1] = *reinterpret_cast<const half4*>(X1 + mc * ldx1 + P + nc);
+            in[i % PF][p][0] = as_half8(ld16(X1 + mc * ldx1 + nc));
+            in[i % PF][p][NL - 1] = as_half8(ld16(X1 + mc * ldx1 + P + nc));
           } else {
-            in[ii][j][0] = *reinterpret_cast<const half4*>(R + mc * ldr + nc);
+            in[i % PF][p][0] = as_half8(ld16(R + mc * ldr + nc));
           }
         }
+      };
+      auto stage_group = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4*>(wr + 16 * j) = acc[i][j];
+      };
+      auto put = [&](lt_half* dst, const half8& v) __attribute__((always_inline)) {
+        if (FULL || EPI != 0 || n + 8 <= N) {
+          st16(dst, as_u32x4(v));
+        } else {
+          // the last 1-7 columns of a ragged N, taken from the packed bits
+          // (the element-indexed form of such stores compiled to stores of
+          // element 0 only)
+          const u32x4 w = as_u32x4(v);
+#pragma unroll
+          for (int e = 0; e < 7; ++e)
+            if (n + e < N) dst[e] = (lt_half)(w[e / 2] >> (16 * (e & 1)));
+        }
+      };
+      if (reads) {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) load_group(i);
       }
-    };
-    auto compute_group = [&](int g) {
+      stage_group(0);
 #pragma unroll
-      for (int ii = 0; ii < IG; ++ii)
+      for (int i = 0; i < TM; ++i) {
+        f32x4 raw[NPASS][EPI == 1 ? 4 : 2];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int i = g * IG + ii;
-          float v[4];
+        for (int p = 0; p < NPASS; ++p) {
+          const float* q = rd + p * RPP * PITCH;
+          raw[p][0] = *reinterpret_cast<const f32x4*>(q);
+          raw[p][1] = *reinterpret_cast<const f32x4*>(q + 4);
+          if constexpr (EPI == 1) {
+            raw[p][2] = *reinterpret_cast<const f32x4*>(q + NC);
+            raw[p][3] = *reinterpret_cast<const f32x4*>(q + NC + 4);
+          }
+        }
+        // (a wave's LDS accesses run in order: the next group may follow at once)
+        if (i + 1 < TM) stage_group(i + 1);
+        // one wait for the group's reads, before their first use
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        float v[NPASS][8], u[EPI == 1 ? NPASS : 1][8];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = alpha * acc[i][j][e];
-          if constexpr (EPI == 2) {
+        for (int p = 0; p < NPASS; ++p)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            v[p][e] = alpha * raw[p][e / 4][e % 4];
+            if constexpr (EPI == 1) u[p][e] = alpha * raw[p][2 + e / 4][e % 4];
+          }
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p) {
+          const int64_t m = mb + i * 16 + p * RPP;
+          const bool on = (FULL || (m < M && n < ncols)) && lane_on;
+          half8 o0, o1, o2;
+          if constexpr (EPI == 1) {
+            // GU[m][n] = G, GU[m][F + n] = U, A[m][n] = silu(G) U (from the
+            // FP32 values, one rounding each)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float g = v[p][e];
+              o0[e] = (_Float16)g;
+              o1[e] = (_Float16)u[p][e];
+              o2[e] = (_Float16)(g * sigmoid_f(g) * u[p][e]);
+            }
+          } else if constexpr (EPI == 2) {
             // v = dA; dG = dA U s (1 + G (1 - s)),  dU = dA silu(G),  s = sigmoid(G)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float gv = (float)in[ii][j][0][e], uv = (float)in[ii][j][1][e];
+            for (int e = 0; e < 8; ++e) {
+              const float gv = (float)in[i % PF][p][0][e], uv = (float)in[i % PF][p][NL - 1][e];
               const float sg = sigmoid_f(gv);
-              out[ii][j][0][e] = (_Float16)(v[e] * uv * sg * (1.f + gv * (1.f - sg)));
-              out[ii][j][1][e] = (_Float16)(v[e] * gv * sg);
+              o0[e] = (_Float16)(v[p][e] * uv * sg * (1.f + gv * (1.f - sg)));
+              o1[e] = (_Float16)(v[p][e] * gv * sg);
             }
           } else {
             if (reads) {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += beta * (float)in[ii][j][0][e];
+              for (int e = 0; e < 8; ++e) v[p][e] += beta * (float)in[i % PF][p][0][e];
             }
             if (has_bias) {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += (float)bv[j][e];
+              for (int e = 0; e < 8; ++e) v[p][e] += (float)bv[e];
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) out[ii][j][0][e] = (_Float16)v[e];
+            for (int e = 0; e < 8; ++e) o0[e] = (_Float16)v[p][e];
+          }
+          if ((FULL && 64 / CH <= 16) || on) {
+            put(C + m * ldc + n, o0);
+            if constexpr (EPI != 0) put(C + m * ldc + P + n, o1);
+            if constexpr (EPI == 1) put(X1 + m * ldx1 + n, o2);
           }
         }
-    };
-    auto store_group = [&](int g) {
-#pragma unroll
-      for (int ii = 0; ii < IG; ++ii) {
-        const int64_t m = mb + (g * IG + ii) * 16;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int64_t n = nb + j * 16;
-          if (m < M && n < N) {
-            if (EPI == 2 || n + 4 <= N) {
-              *reinterpret_cast<half4*>(C + m * ldc + n) = out[ii][j][0];
-              if constexpr (EPI == 2)
-                *reinterpret_cast<half4*>(C + m * ldc + P + n) = out[ii][j][1];
-            } else {
-              // the last 1-3 columns of a ragged N (plain epilogue only),
-              // taken from the packed bits (the element-indexed form of
-              // these stores compiled to stores of element 0 only)
-              const uint64_t bits = __builtin_bit_cast(uint64_t, out[ii][j][0]);
-              C[m * ldc + n] = (lt_half)bits;
-              if (n + 1 < N) C[m * ldc + n + 1] = (lt_half)(bits >> 16);
-              if (n + 2 < N) C[m * ldc + n + 2] = (lt_half)(bits >> 32);
-            }
-          }
-        }
+        if (reads && i + PF < TM) load_group(i + PF);
       }
     };
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if (reads) load_group(g);
-      if (g > 0) store_group(g - 1);
-      compute_group(g);
-    }
-    store_group(NG - 1);
+    if (m0 + BM <= M && n0 + (EPI == 1 ? BN / 2 : BN) <= ncols)
+      finish(std::true_type{});
+    else
+      finish(std::false_type{});
   }
 }
 

@@ -78,18 +78,18 @@ constexpr int64_t kPlanCUs = 256;
 // epilogues and, in the plain one, for reading R.  Fitted to calls whose
 // operands come from HBM, as a program's weights and activations do (calls
 // on cached operands run 10-25% faster, the smaller tiles most): 1024 x 4096 x
-// {4096, 11008} NT take 103 / 264 us as 256x256 tiles, 59.5 / 156 as 256x128,
-// 42 / 111 as 128x128, 77 / 195 as 64x64; 4096 x 4096 x {4096, 11008} 112 / 286,
-// 124 / 317, 155 / 417, 296 / 749.
+// {4096, 11008} NT take 96 / 257 us as 256x256 tiles, 57 / 154 as 256x128,
+// 42 / 110 as 128x128, 77 / 194 as 64x64; 4096 x 4096 x {4096, 11008} 109 / 285,
+// 123 / 321, 154 / 411, 297 / 745.
 struct TileCost {
   double slice, slice_tn, load, fixed[3], r;
 };
 constexpr TileCost kTileCost[kNumGemmTiles] = {
-    {1.46, 1.33, 0.10, {8.0, 10.0, 28.0}, 8.0},
-    {0.87, 0.91, 0.03, {4.0, 5.0, 16.0}, 4.0},
-    {0.88, 0.92, 0.03, {4.0, 5.0, 16.0}, 4.0},
-    {0.50, 0.52, 0.10, {1.5, 2.0, 9.0}, 2.0},
-    {0.25, 0.26, 0.02, {1.5, 3.0, 7.0}, 0.5},
+    {1.48, 1.42, 0.10, {4.0, 6.0, 18.0}, 6.0},
+    {0.87, 0.92, 0.03, {3.0, 4.5, 11.0}, 3.0},
+    {0.87, 0.92, 0.03, {3.0, 4.5, 13.0}, 3.0},
+    {0.50, 0.55, 0.10, {1.5, 2.0, 6.0}, 1.5},
+    {0.25, 0.26, 0.02, {1.5, 3.0, 5.5}, 0.5},
 };
 constexpr double kLaunchUs = 4.0;             // a further launch in the stream
 constexpr double kPartialBytesPerUs = 9.0e6;  // split-K partials, written, then read
