@@ -205,9 +205,8 @@ struct RmsBwdArgs {
   int64_t T, H;
 };
 constexpr int kRmsBwdWaves = 4;
-// One row per wave up to 2048 rows, then at most 512 workgroups (two rows per
-// wave at T = 4096): a wave's second row loads while other waves store their
-// first, and the dW pass has half the partial rows of one row per wave.
+// Four rows per workgroup up to 2048 rows, then at most 512 workgroups (two
+// per CU; eight rows each at T = 4096).
 inline int rmsnorm_bwd_blocks(int64_t T) {
   const int64_t b = T / kRmsBwdWaves + (T % kRmsBwdWaves != 0);   // no overflow at any T
   return (int)(b < 512 ? (b < 1 ? 1 : b) : 512);

@@ -6,17 +6,13 @@
 //     l, l + 64, ... of the row (coalesced), the sum of squares is a wave
 //     shuffle reduction; writes y = w * x * r (one rounding) and r.
 //       r = (mean_j x_j^2 + eps)^(-1/2)
-//   * rmsnorm_bwd: the same row layout, 4 waves per workgroup, one row per
-//     wave for short inputs and a few for long ones (at most 512
-//     workgroups); per row
+//   * rmsnorm_bwd: workgroups of 4 waves (at most 512), all of a workgroup on
+//     one row at a time; per row
 //       dx = r * w * g - r^3 * x / H * sum_j g_j w_j x_j   (+ residual R)
-//     with g and x held in registers between the row dot product and dx
-//     (rows up to 6144 columns; wider rows are read twice, the second time
-//     from L2).  Every wave keeps the FP32 partial of dw = sum_rows g * x * r
-//     for the rows it visits; the workgroup adds its waves' partials in wave
-//     order through LDS, writes one partial row to the workspace, and
-//     rmsnorm_dw_sum adds those rows in a fixed order (deterministic, no
-//     atomics).
+//     with g, x and R read once, into registers, one row ahead.  Every thread
+//     keeps the FP32 partial of dw = sum_rows g * x * r for its columns; the
+//     workgroup writes one partial row to the workspace, and rmsnorm_dw_sum
+//     adds those rows in a fixed order (deterministic, no atomics).
 //   * rope_table: cos / sin of p * base^(-2i/D) for p < S, i < D/2, with the
 //     angle formed and reduced in FP64 (positions up to 10^4 and more keep
 //     full FP32 accuracy), stored as FP32 pairs.
@@ -76,104 +72,110 @@ rmsnorm_fwd_kernel(const lt_half* __restrict__ X, int64_t ldx, const lt_half* __
 }
 
 // ---------------------------------------------------------------- backward
-// Workgroup = kBwdWaves waves over a contiguous range of rows; wave w takes
-// rows row0 + w, row0 + w + kBwdWaves, ...  Every wave accumulates its dw
-// partial for all columns in registers; at the end the workgroup adds its
-// waves' partials in wave order through LDS (8 columns per lane at a time)
-// and writes one partial row, blockIdx.x, of the workspace [nblk][H] FP32.
+// Workgroups of kBwdWaves waves, the whole workgroup on one row at a time: thread t owns the 16-byte chunks t, t + 256,
+// ... of every row, so its w and its FP32 dw partial stay in registers (KPT
+// chunks) and the workgroup's partial row needs no further sum.  HBM-bound
+// (g, x, R in, dx out): the next row's loads are in flight while the current
+// row's dot product goes through the waves (one barrier a row, sums in wave
+// order).  With one wave per row a row's 30 KB were loaded, reduced and
+// written in turn by 8 waves a CU: 4096 x 5120 took 52 us (3.2 TB/s), now 41.
 constexpr int kBwdWaves = kRmsBwdWaves;
+constexpr int kBwdThreads = 64 * kBwdWaves;
 
-template <int MAXK, bool ONEPASS>
-__global__ void __launch_bounds__(64 * kBwdWaves)
+template <int KPT>
+__global__ void __launch_bounds__(kBwdThreads)
 rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* __restrict__ X,
                    int64_t ldx, const lt_half* __restrict__ W, const float* __restrict__ RSTD,
                    const lt_half* __restrict__ R, int64_t ldr, lt_half* __restrict__ dX,
-                   int64_t lddx, float* __restrict__ part, int64_t T, int H, int rows_per_wg) {
-  __shared__ float red[kBwdWaves][64 * 8];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+                   int64_t lddx, float* __restrict__ part, int64_t T, int H) {
+  __shared__ float red[2][kBwdWaves];
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6;
   const int nch = H / 8;
-  const int64_t row0 = (int64_t)blockIdx.x * rows_per_wg;
-  const int64_t row_end = row0 + rows_per_wg < T ? row0 + rows_per_wg : T;
   const float inv_h = 1.f / (float)H;
+  const u32x4 zero = {0, 0, 0, 0};
 
-  float dw[MAXK][8];
+  half8 wv[KPT];
+  float dw[KPT][8];
 #pragma unroll
-  for (int k = 0; k < MAXK; ++k)
+  for (int k = 0; k < KPT; ++k) {
+    const int c = tid + kBwdThreads * k;
+    wv[k] = as_half8(c < nch ? ld16(W + c * 8) : zero);
 #pragma unroll
     for (int e = 0; e < 8; ++e) dw[k][e] = 0.f;
+  }
 
-  // ONEPASS: the row's g and x stay in registers between the dot product
-  // and dx; otherwise (wide rows) the second pass re-reads them (L2).
-  for (int64_t row = row0 + wave; row < row_end; row += kBwdWaves) {
-    const float r = RSTD[row];
-    const lt_half* gp = dY + row * lddy;
-    const lt_half* xp = X + row * ldx;
-    half8 gk[ONEPASS ? MAXK : 1], xk[ONEPASS ? MAXK : 1], rk[ONEPASS ? MAXK : 1];
-    float dot = 0.f;
+  struct Row {
+    half8 g[KPT], x[KPT], r[KPT];
+    float rstd;
+  };
+  auto load = [&](int64_t row, Row& v) __attribute__((always_inline)) {
+    v.rstd = RSTD[row];
 #pragma unroll
-    for (int k = 0; k < MAXK; ++k) {
-      const int c = lane + 64 * k;
-      half8 gv = as_half8(u32x4{0, 0, 0, 0}), xv = gv, rv = gv;
+    for (int k = 0; k < KPT; ++k) {
+      const int c = tid + kBwdThreads * k;
+      v.g[k] = v.x[k] = v.r[k] = as_half8(zero);
       if (c < nch) {
-        gv = as_half8(ld16(gp + c * 8));
-        xv = as_half8(ld16(xp + c * 8));
-        // rows up to 4096 columns: the residual row is loaded with g and x
-        // (one memory latency per row); wider rows load it later, for registers
-        if (ONEPASS && MAXK <= 8 && R) rv = as_half8(ld16(R + row * ldr + c * 8));
-        const half8 wv = as_half8(ld16(W + c * 8));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dot += (float)gv[e] * (float)wv[e] * (float)xv[e];
-      }
-      if constexpr (ONEPASS) {
-        gk[k] = gv;
-        xk[k] = xv;
-        rk[k] = rv;
+        v.g[k] = as_half8(ld16(dY + row * lddy + c * 8));
+        v.x[k] = as_half8(ld16(X + row * ldx + c * 8));
+        if (R) v.r[k] = as_half8(ld16(R + row * ldr + c * 8));
       }
     }
+  };
+  // every thread of the workgroup takes the same rows (barrier inside)
+  auto finish = [&](int64_t row, const Row& v, int buf) __attribute__((always_inline)) {
+    float dot = 0.f;
+#pragma unroll
+    for (int k = 0; k < KPT; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dot += (float)v.g[k][e] * (float)wv[k][e] * (float)v.x[k][e];
     dot = wave_sum(dot);
-    const float c3 = r * r * r * dot * inv_h;
+    if ((tid & 63) == 0) red[buf][wave] = dot;
+    __syncthreads();
+    float sum = 0.f;
 #pragma unroll
-    for (int k = 0; k < MAXK; ++k) {
-      const int c = lane + 64 * k;
-      if (c < nch) {
-        const half8 gv = ONEPASS ? gk[k] : as_half8(ld16(gp + c * 8));
-        const half8 xv = ONEPASS ? xk[k] : as_half8(ld16(xp + c * 8));
-        const half8 wv = as_half8(ld16(W + c * 8));
-        half8 rv = as_half8(u32x4{0, 0, 0, 0});
-        if (ONEPASS && MAXK <= 8) rv = rk[k];
-        else if (R) rv = as_half8(ld16(R + row * ldr + c * 8));
-        half8 o;
+    for (int q = 0; q < kBwdWaves; ++q) sum += red[buf][q];
+    const float r = v.rstd;
+    const float c3 = r * r * r * sum * inv_h;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float g = (float)gv[e], x = (float)xv[e];
-          dw[k][e] += g * x * r;
-          o[e] = (_Float16)((float)rv[e] + (r * (float)wv[e] * g - c3 * x));
-        }
-        st16(dX + row * lddx + c * 8, as_u32x4(o));
+    for (int k = 0; k < KPT; ++k) {
+      const int c = tid + kBwdThreads * k;
+      half8 o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float g = (float)v.g[k][e], x = (float)v.x[k][e];
+        dw[k][e] += g * x * r;
+        o[e] = (_Float16)((float)v.r[k][e] + (r * (float)wv[k][e] * g - c3 * x));
       }
+      if (c < nch) st16(dX + row * lddx + c * 8, as_u32x4(o));
+    }
+  };
+
+  // rows blockIdx.x, + gridDim.x, ...: the workgroups sweep the arrays together
+  // (a contiguous range each: 43 us against 41 at 4096 x 5120; a third row in
+  // flight changes nothing).  Two rows per trip: two register sets, two reduction slots (a slot is written
+  // again only after the barrier of the row between).
+  const int64_t step = gridDim.x;
+  if (blockIdx.x < T) {
+    Row a, b;
+    load(blockIdx.x, a);
+    for (int64_t row = blockIdx.x; row < T; row += 2 * step) {
+      if (row + step < T) load(row + step, b);
+      finish(row, a, 0);
+      if (row + step >= T) break;
+      if (row + 2 * step < T) load(row + 2 * step, a);
+      finish(row + step, b, 1);
     }
   }
 
-  // workgroup sum of the waves' partials, 512 columns at a time, in wave order
   float* dst = part + (int64_t)blockIdx.x * H;
 #pragma unroll
-  for (int k = 0; k < MAXK; ++k) {
-    if (64 * k >= nch) break;                       // uniform
-#pragma unroll
-    for (int e = 0; e < 8; ++e) red[wave][lane * 8 + e] = dw[k][e];
-    __syncthreads();
-    // columns 512 k + t, t = thread, thread + 64 kBwdWaves, ...
-#pragma unroll
-    for (int t = threadIdx.x; t < 512; t += 64 * kBwdWaves) {
-      if (64 * k + t / 8 < nch) {
-        float sum = 0.f;
-#pragma unroll
-        for (int v = 0; v < kBwdWaves; ++v) sum += red[v][t];
-        dst[512 * k + t] = sum;
-      }
+  for (int k = 0; k < KPT; ++k) {
+    const int c = tid + kBwdThreads * k;
+    if (c < nch) {
+      *reinterpret_cast<float4*>(dst + c * 8) = make_float4(dw[k][0], dw[k][1], dw[k][2], dw[k][3]);
+      *reinterpret_cast<float4*>(dst + c * 8 + 4) = make_float4(dw[k][4], dw[k][5], dw[k][6], dw[k][7]);
     }
-    __syncthreads();
   }
 }
 
@@ -274,13 +276,12 @@ hipError_t launch_rms_fwd(const lt_half* X, int64_t ldx, const lt_half* W, lt_ha
   return hipGetLastError();
 }
 
-template <int MAXK, bool ONEPASS>
+template <int KPT>
 hipError_t launch_rms_bwd(const RmsBwdArgs& a, hipStream_t s) {
   const int nblk = rmsnorm_bwd_blocks(a.T);
-  const int rows_per_wg = (int)((a.T + nblk - 1) / nblk);
-  hipLaunchKernelGGL((rmsnorm_bwd_kernel<MAXK, ONEPASS>), dim3((unsigned)nblk), dim3(64 * kBwdWaves), 0, s,
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<KPT>), dim3((unsigned)nblk), dim3(kBwdThreads), 0, s,
                      a.dY, a.lddy, a.X, a.ldx, a.W, a.RSTD, a.R, a.ldr, a.dX, a.lddx, a.part, a.T,
-                     (int)a.H, rows_per_wg);
+                     (int)a.H);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(rmsnorm_dw_sum_kernel, dim3((unsigned)((a.H + 63) / 64)), dim3(64 * kSumWaves),
@@ -301,11 +302,12 @@ hipError_t rmsnorm_fwd_launch(const lt_half* X, int64_t ldx, const lt_half* W, l
 }
 
 hipError_t rmsnorm_bwd_launch(const RmsBwdArgs& a, hipStream_t s) {
-  const int64_t k = (a.H / 8 + 63) / 64;
-  if (k <= 4) return launch_rms_bwd<4, true>(a, s);
-  if (k <= 8) return launch_rms_bwd<8, true>(a, s);
-  if (k <= 12) return launch_rms_bwd<12, true>(a, s);
-  return launch_rms_bwd<16, false>(a, s);
+  switch ((a.H / 8 + kBwdThreads - 1) / kBwdThreads) {   // chunks per thread: H <= 8192
+    case 1: return launch_rms_bwd<1>(a, s);
+    case 2: return launch_rms_bwd<2>(a, s);
+    case 3: return launch_rms_bwd<3>(a, s);
+    default: return launch_rms_bwd<4>(a, s);
+  }
 }
 
 hipError_t rope_table_launch(float* CS, int S, int D, double base, hipStream_t s) {
