@@ -29,11 +29,11 @@
 //                     sequences, few kv heads) the tiles hold 128 keys: waves
 //                     w and w + 4 own the same keys, take the two 32-query
 //                     halves of each block, and add their accumulators
-//                     through LDS at the end.  Still too few: each key tile's
+//                     through LDS at the end.  Still too few: a key tile's
 //                     (query head, query block) work is split over several
-//                     workgroups, whose FP32 partial dK, dV go to the
-//                     workspace and are summed in a fixed order by
-//                     attn_bwd_dkdv_sum.
+//                     workgroups in proportion to its length, whose FP32
+//                     partial dK, dV go to the workspace and are summed in a
+//                     fixed order by attn_bwd_dkdv_sum.
 //   3. attn_bwd_dq  : GQ = GS K from the stored dS, query-major: one workgroup
 //                     per (batch, head, 256 queries), each wave one 32-query
 //                     group, streaming K slices (shared, LDS) and its own dS
@@ -232,7 +232,8 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
                      const float* __restrict__ delta, lt_half* __restrict__ dK,
                      lt_half* __restrict__ dV, int64_t dkv_stride, lt_half* __restrict__ ds_out,
                      const lt_half* __restrict__ psaved, int64_t nblk, float* __restrict__ part,
-                     int nsplit, int B, int S, int Hq, int Hkv, float scale, int causal) {
+                     int nsplit, const DkdvShares shares, int B, int S, int Hq, int Hkv, float scale,
+                     int causal) {
   using SM = DkdvSmem<D>;
   using RT = RowTile<D, NWA>;
   constexpr int KK = D / 16;       // MFMA steps over the head dim
@@ -252,8 +253,21 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
   const int kpart = wave / NKG;                    // query half taken (KSPLIT = 2)
 
   const int bkv = blockIdx.x % (B * Hkv);
-  const int sp = (blockIdx.x / (B * Hkv)) % nsplit;   // which share of the query blocks
-  const int jt = blockIdx.x / (B * Hkv * nsplit);     // ascending key tile = descending work
+  // slots in ascending key tile order = descending work
+  const int slot = blockIdx.x / (B * Hkv);
+  int jt = slot, sp = 0, nsh = 1;                     // key tile, share of its query blocks, shares
+  if (nsplit > 1) {
+    const int n_kt = (S + BK - 1) / BK;
+    int lo = 0, hi = n_kt - 1;                        // last tile with off[tile] <= slot
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) / 2;
+      if (shares.off[mid] <= slot) lo = mid;
+      else hi = mid - 1;
+    }
+    jt = lo;
+    sp = slot - shares.off[jt];
+    nsh = shares.off[jt + 1] - shares.off[jt];
+  }
   const int b = bkv / Hkv;
   const int kvh = bkv % Hkv;
   const int G = Hq / Hkv;                             // query heads of the kv head
@@ -298,11 +312,10 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
   const int qb0 = causal ? kbase / BQA : 0;
   const int per_head = n_qb - qb0;
   // The group's (query head, query block) pairs, head-major, are split into
-  // nsplit contiguous shares; this workgroup takes share sp (possibly empty:
-  // its partial sums are then zero).
+  // nsh contiguous shares; this workgroup takes share sp.
   const int total = G * per_head;
-  const int it0 = (int)((int64_t)sp * total / nsplit);
-  const int n_iter = (int)((int64_t)(sp + 1) * total / nsplit) - it0;
+  const int it0 = (int)((int64_t)sp * total / nsh);
+  const int n_iter = (int)((int64_t)(sp + 1) * total / nsh) - it0;
 
   // Block `it` = (query head, 64 queries).  Q, dO (rows past S read as zero)
   // and the base-2 LSE and D entries (zero past S: with zero Q and dO rows
@@ -647,12 +660,12 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
       }
   }
 
-  // ---- write dK = scale * acc, dV (or this split's FP32 partial sums) ----
-  if (nsplit > 1) {
+  // ---- write dK = scale * acc, dV (or this share's FP32 partial sums) ----
+  if (nsh > 1) {
     if (mykey < S) {
-      const int64_t rowsz = (int64_t)B * S * Hkv * D;
-      float* pk = part + (int64_t)sp * rowsz + (((int64_t)b * S + mykey) * Hkv + kvh) * D;
-      float* pv = pk + (int64_t)nsplit * rowsz;
+      const int rows = BK < S ? BK : S;
+      float* pk = part + (((int64_t)bkv * shares.m + slot) * rows + (mykey - kbase)) * D;
+      float* pv = pk + (int64_t)B * Hkv * shares.m * rows * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1097,29 +1110,37 @@ attn_bwd_rowterms_kernel(const lt_half* __restrict__ O, const lt_half* __restric
 }
 
 // ------------------------------------------------------------ kernel 2b: dK/dV share sum
-// Grouped queries split over several dK/dV workgroups: dK = scale * sum of
-// the FP32 partials, dV = sum, in split order (deterministic).  HBM-bound.
+// Key tiles split over several dK/dV workgroups: dK = scale * sum of the FP32
+// partials, dV = sum, in share order (deterministic).  Tiles of one share
+// were written directly.  HBM-bound.
 template <int D>
 __global__ void __launch_bounds__(256)
-attn_bwd_dkdv_sum_kernel(const float* __restrict__ part, int nsplit, lt_half* __restrict__ dK,
-                         lt_half* __restrict__ dV, int64_t dkv_stride, int B, int S, int Hkv,
-                         float scale) {
+attn_bwd_dkdv_sum_kernel(const float* __restrict__ part, const DkdvShares shares, int ktile,
+                         lt_half* __restrict__ dK, lt_half* __restrict__ dV, int64_t dkv_stride, int B,
+                         int S, int Hkv, float scale) {
   constexpr int CPR = D / 8;                       // 8-element chunks per row
-  const int64_t rowsz = (int64_t)B * S * Hkv * D;
   const int64_t chunks = (int64_t)B * S * Hkv * CPR;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= chunks) return;
-  const int64_t e0 = gid * 8;                      // element offset in [B*S][Hkv][D]
-  const int64_t bs = gid / (Hkv * CPR);
-  const int kvh = (int)((gid / CPR) % Hkv);
+  // threads in [B, Hkv][S][D] order: the partials' rows are read in a row
   const int d0 = (int)(gid % CPR) * 8;
+  const int key = (int)((gid / CPR) % S);
+  const int bkv = (int)(gid / ((int64_t)CPR * S));
+  const int b = bkv / Hkv, kvh = bkv % Hkv;
+  const int jt = key / ktile;
+  const int t0 = shares.off[jt], t1 = shares.off[jt + 1];
+  if (t1 - t0 == 1) return;
+  const int rows = ktile < S ? ktile : S;
+  const int64_t slotsz = (int64_t)rows * D;
+  const int64_t bs = (int64_t)b * S + key;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
-    const float* src = part + (int64_t)which * nsplit * rowsz + e0;
+    const float* src = part + ((int64_t)(which * B * Hkv + bkv) * shares.m) * slotsz +
+                       (int64_t)(key - jt * ktile) * D + d0;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int t = 0; t < nsplit; ++t) {
-      const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)t * rowsz);
-      const float4 y = *reinterpret_cast<const float4*>(src + (int64_t)t * rowsz + 4);
+    for (int t = t0; t < t1; ++t) {
+      const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)t * slotsz);
+      const float4 y = *reinterpret_cast<const float4*>(src + (int64_t)t * slotsz + 4);
       acc[0] += x.x; acc[1] += x.y; acc[2] += x.z; acc[3] += x.w;
       acc[4] += y.x; acc[5] += y.y; acc[6] += y.z; acc[7] += y.w;
     }
@@ -1146,16 +1167,16 @@ hipError_t launch_bwd(const AttnBwdArgs& a, hipStream_t s) {
   }
   // 2. dK, dV (and their share sum), storing dS
   const int n_kt = (sh.S + a.ktile - 1) / a.ktile;
-  const dim3 kgrid((unsigned)(n_kt * sh.B * sh.Hkv * a.nsplit));
+  const dim3 kgrid((unsigned)((a.nsplit > 1 ? a.shares.m : n_kt) * sh.B * sh.Hkv));
   if (a.ktile == BKV)
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 1, false>), kgrid, dim3(NWA * 64), 0, s, a.Q,
                        a.K, a.V, a.q_stride, a.kv_stride, a.dO, a.o_stride, a.lse2, a.delta, a.dK,
-                       a.dV, a.dkv_stride, a.ds, nullptr, nblk, a.part, a.nsplit, sh.B, sh.S,
+                       a.dV, a.dkv_stride, a.ds, nullptr, nblk, a.part, a.nsplit, a.shares, sh.B, sh.S,
                        sh.Hq, sh.Hkv, sh.scale, sh.causal);
   else if (a.ktile == BKV / 2)
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 2, false>), kgrid, dim3(NWA * 64), 0, s, a.Q,
                        a.K, a.V, a.q_stride, a.kv_stride, a.dO, a.o_stride, a.lse2, a.delta, a.dK,
-                       a.dV, a.dkv_stride, a.ds, nullptr, nblk, a.part, a.nsplit, sh.B, sh.S,
+                       a.dV, a.dkv_stride, a.ds, nullptr, nblk, a.part, a.nsplit, a.shares, sh.B, sh.S,
                        sh.Hq, sh.Hkv, sh.scale, sh.causal);
   else
     return hipErrorInvalidValue;
@@ -1164,7 +1185,7 @@ hipError_t launch_bwd(const AttnBwdArgs& a, hipStream_t s) {
   if (a.nsplit > 1) {
     const int64_t chunks = (int64_t)sh.B * sh.S * sh.Hkv * (D / 8);
     hipLaunchKernelGGL((attn_bwd_dkdv_sum_kernel<D>), dim3((unsigned)((chunks + 255) / 256)),
-                       dim3(256), 0, s, a.part, a.nsplit, a.dK, a.dV, a.dkv_stride, sh.B, sh.S,
+                       dim3(256), 0, s, a.part, a.shares, a.ktile, a.dK, a.dV, a.dkv_stride, sh.B, sh.S,
                        sh.Hkv, sh.scale);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1211,16 +1232,16 @@ hipError_t launch_bwd_p(const AttnBwdArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int64_t nblk = attn_bwd_ds_blocks(sh.S, sh.causal);
   const int n_kt = (sh.S + a.ktile - 1) / a.ktile;
-  const dim3 kgrid((unsigned)(n_kt * sh.B * sh.Hkv * a.nsplit));
+  const dim3 kgrid((unsigned)((a.nsplit > 1 ? a.shares.m : n_kt) * sh.B * sh.Hkv));
   if (a.ktile == BKV)
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 1, true>), kgrid, dim3(NWA * 64), 0, s, a.Q, a.K,
                        a.V, a.q_stride, a.kv_stride, a.dO, a.o_stride, a.lse2, a.delta, a.dK,
-                       a.dV, a.dkv_stride, nullptr, a.psaved, nblk, a.part, a.nsplit, sh.B, sh.S,
+                       a.dV, a.dkv_stride, nullptr, a.psaved, nblk, a.part, a.nsplit, a.shares, sh.B, sh.S,
                        sh.Hq, sh.Hkv, sh.scale, sh.causal);
   else if (a.ktile == BKV / 2)
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, 2, true>), kgrid, dim3(NWA * 64), 0, s, a.Q, a.K,
                        a.V, a.q_stride, a.kv_stride, a.dO, a.o_stride, a.lse2, a.delta, a.dK,
-                       a.dV, a.dkv_stride, nullptr, a.psaved, nblk, a.part, a.nsplit, sh.B, sh.S,
+                       a.dV, a.dkv_stride, nullptr, a.psaved, nblk, a.part, a.nsplit, a.shares, sh.B, sh.S,
                        sh.Hq, sh.Hkv, sh.scale, sh.causal);
   else
     return hipErrorInvalidValue;
@@ -1229,7 +1250,7 @@ hipError_t launch_bwd_p(const AttnBwdArgs& a, hipStream_t s) {
   if (a.nsplit > 1) {
     const int64_t chunks = (int64_t)sh.B * sh.S * sh.Hkv * (D / 8);
     hipLaunchKernelGGL((attn_bwd_dkdv_sum_kernel<D>), dim3((unsigned)((chunks + 255) / 256)),
-                       dim3(256), 0, s, a.part, a.nsplit, a.dK, a.dV, a.dkv_stride, sh.B, sh.S,
+                       dim3(256), 0, s, a.part, a.shares, a.ktile, a.dK, a.dV, a.dkv_stride, sh.B, sh.S,
                        sh.Hkv, sh.scale);
     e = hipGetLastError();
   }

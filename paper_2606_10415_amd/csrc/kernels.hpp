@@ -92,6 +92,14 @@ struct AttnFwdArgs {
   float* LSE;
 };
 
+// Shares of the key tiles' work in the dK/dV pass: key tile j of every (batch,
+// kv head) is done by workgroups (slots) off[j] .. off[j + 1] - 1 of m.
+constexpr int kMaxSplitTiles = 512;   // a split has tiles x B x Hkv < 512
+struct DkdvShares {
+  int m;
+  uint16_t off[kMaxSplitTiles + 1];
+};
+
 struct AttnBwdArgs {
   AttnShape sh;
   const lt_half* Q;
@@ -109,10 +117,11 @@ struct AttnBwdArgs {
   float* delta;   // workspace: [B, Hq, S]  rowsum(dO * O)
   float* lse2;    // workspace: [B, Hq, S]  LSE * log2(e)
   lt_half* ds;    // workspace: dS blocks [B, Hq, n_blocks(S, causal)][64 lanes][16] FP16
-  float* part;    // workspace: [2][nsplit][B, S, Hkv, D] partial dK, dV (nsplit > 1 only)
-  int nsplit;     // shares of each key tile's work in the dK/dV pass
+  float* part;    // workspace: [2][B, Hkv][slot][min(ktile, S)][D] partial dK, dV (nsplit > 1 only)
+  int nsplit;     // 1: one workgroup per key tile; else the key tiles are split by `shares`
   int ktile;      // keys per dK/dV workgroup (256 or 128)
   const lt_half* psaved = nullptr;   // saved P blocks (saved-P backward only)
+  DkdvShares shares = {};            // nsplit > 1 only
 };
 
 // Saved P (written after the forward, read by the saved-P backward): the
@@ -160,10 +169,12 @@ inline size_t attn_bwd_ds_bytes(int B, int S, int Hq, int causal) {
 //   * otherwise n = min(max(Hq/Hkv, ceil(256 / tiles)), 16, the pairs of
 //     the last key tile, which has the fewest) -- e.g. a short causal MHA
 //     sequence.
+// n sizes the workspace (partial rows for n shares of every key); how many
+// shares each tile gets within it is attn_bwd_shares' choice.
 constexpr int64_t kDkdvFillWgs = 256;   // fallback split target: one workgroup per CU
 struct DkdvPlan {
   int ktile;    // keys per workgroup: 256 or 128
-  int nsplit;   // shares of each key tile's work
+  int nsplit;   // shares of each key tile's work the workspace has room for
 };
 inline DkdvPlan attn_bwd_dkdv_plan(int B, int S, int Hq, int Hkv) {
   const int grp = Hq / Hkv;
@@ -185,6 +196,70 @@ inline DkdvPlan attn_bwd_dkdv_plan(int B, int S, int Hq, int Hkv) {
 inline size_t attn_bwd_part_bytes(int B, int S, int Hq, int Hkv, int D) {
   const int n = attn_bwd_dkdv_plan(B, S, Hq, Hkv).nsplit;
   return n > 1 ? align256((size_t)2 * n * B * S * Hkv * D * sizeof(float)) : 0;
+}
+
+// Shares per key tile: enough for one to four rounds of workgroups (one per
+// CU), in proportion to the tiles' work -- under the causal mask the first
+// tile has many times the last one's, and equal shares leave the CUs waiting
+// for its workgroups -- within the workspace's rows for nsplit equal shares.
+// Returns false where one workgroup per tile is estimated no slower (no
+// partials and no sum pass then).
+//   Equal shares of one query head each, 2048 tokens of 40:8 heads: 320
+//   workgroups of 32 .. 4 blocks for 256 CUs, dK/dV pass 122 us; 256 of at
+//   most 25 blocks: 97 us.
+inline bool attn_bwd_shares(int B, int S, int Hq, int Hkv, int D, int causal, const DkdvPlan& plan,
+                            DkdvShares* out) {
+  constexpr int64_t kCUs = 256;
+  const int n_kt = (S - 1) / plan.ktile + 1, n_qb = (S - 1) / 64 + 1;
+  if (plan.nsplit <= 1 || n_kt > kMaxSplitTiles) return false;
+  const int64_t heads = (int64_t)B * Hkv, grp = Hq / Hkv;
+  auto work = [&](int j) { return grp * (n_qb - (causal ? (int64_t)j * (plan.ktile / 64) : 0)); };
+  // partial rows: a slot holds one tile's (at most S) keys
+  const int64_t slots_max = n_kt == 1 ? plan.nsplit : (int64_t)plan.nsplit * S / plan.ktile;
+  int64_t total = 0;
+  for (int j = 0; j < n_kt; ++j) total += work(j);
+  // slots with no workgroup above c blocks
+  auto slots = [&](int64_t c) {
+    int64_t m = 0;
+    for (int j = 0; j < n_kt; ++j) m += (work(j) + c - 1) / c;
+    return m;
+  };
+  // us of the pass: a 64-query block of a 256-key tile takes 5.7 us at D =
+  // 128, starting and ending a workgroup about 6; the sum pass streams the
+  // partials at about 6 TB/s
+  auto cost = [&](int64_t c, int64_t m) {
+    const int64_t wgs = m * heads, rounds = (wgs + kCUs - 1) / kCUs;
+    const double avg = (double)(total * heads) / kCUs, longest = (double)c;
+    const double blocks = rounds == 1 ? longest : (avg > longest ? avg : longest) + 0.35 * longest;
+    const double us = blocks * (D == 128 ? 5.7 : 3.5) * plan.ktile / 256 + 6.0 * (double)rounds;
+    return m == n_kt ? us : us + 4.0 + (double)wgs * plan.ktile * D * 8 / 6.0e6;
+  };
+  int64_t best_c = work(0);
+  double best = cost(best_c, n_kt);
+  for (int64_t r = 1; r <= 4; ++r) {
+    int64_t m = r * kCUs / heads;
+    if (m > slots_max) m = slots_max;
+    if (m <= n_kt) continue;
+    int64_t lo = 1, hi = work(0);      // smallest c with slots(c) <= m
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (slots(mid) <= m) hi = mid;
+      else lo = mid + 1;
+    }
+    const double us = cost(lo, slots(lo));
+    if (us < best) {
+      best = us;
+      best_c = lo;
+    }
+  }
+  int64_t m = 0;
+  for (int j = 0; j < n_kt; ++j) {
+    out->off[j] = (uint16_t)m;
+    m += (work(j) + best_c - 1) / best_c;
+  }
+  out->off[n_kt] = (uint16_t)m;
+  out->m = (int)m;
+  return m > n_kt;
 }
 
 // RMSNorm backward (norm_rope.hip).  dW partial sums: one FP32 row of H per

@@ -283,7 +283,7 @@ lt_status lt_attn_bwd(const lt_half* Q, const lt_half* K, const lt_half* V, int6
                     reinterpret_cast<float*>(ws + off_part),
                     0, 0};
   const lt::DkdvPlan plan = lt::attn_bwd_dkdv_plan(B, S, Hq, Hkv);
-  a.nsplit = plan.nsplit;
+  a.nsplit = lt::attn_bwd_shares(B, S, Hq, Hkv, D, causal, plan, &a.shares) ? plan.nsplit : 1;
   a.ktile = plan.ktile;
   return from_hip(lt::attn_bwd_launch(a, reinterpret_cast<hipStream_t>(stream)), "attn_bwd launch");
 }
@@ -350,9 +350,10 @@ lt_status lt_attn_bwd_p(const lt_half* Q, const lt_half* K, const lt_half* V, in
                     reinterpret_cast<float*>(ws + off_lse2),
                     nullptr,
                     reinterpret_cast<float*>(ws + off_part),
-                    0, 0, P};
+                    0, 0};
+  a.psaved = P;
   const lt::DkdvPlan plan = lt::attn_bwd_dkdv_plan(B, S, Hq, Hkv);
-  a.nsplit = plan.nsplit;
+  a.nsplit = lt::attn_bwd_shares(B, S, Hq, Hkv, D, causal, plan, &a.shares) ? plan.nsplit : 1;
   a.ktile = plan.ktile;
   return from_hip(lt::attn_bwd_p_launch(a, reinterpret_cast<hipStream_t>(stream)),
                   "attn_bwd_p launch");
