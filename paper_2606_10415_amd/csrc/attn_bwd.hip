@@ -79,6 +79,8 @@ constexpr int NW = 8;          // recomputing dQ: waves per workgroup
 constexpr int BQB = NW * 32;   // recomputing dQ: queries per workgroup (32 per wave)
 constexpr int BKB = 128;       // recomputing dQ: keys per slice
 constexpr int64_t kDqFillWgs = 512;   // recomputing dQ: 256-query workgroups needed to skip the split
+constexpr int64_t kDqHalfWgs = 128;   // dQ from dS: 256-query workgroups up to which they hold 128
+constexpr int64_t kSavePFillWgs = 1024;   // saved P: workgroups aimed at
 constexpr float kLog2e = 1.4426950408889634f;
 
 // ------------------------------------------------------------ kernel 0: saved P
@@ -87,10 +89,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 // loads the forward's probability tiles instead of recomputing them).  Same
 // lane layout and block order as the dS blocks, so the dK/dV pass loads each
 // lane's P straight into registers.  Masked entries (key after query, key or
-// query past S) are exactly 0.  One workgroup per (batch, query head,
-// 256-key tile): 8 waves of 32 keys (K fragments in registers); 64-query Q
-// blocks and their LSE rows stream through LDS by direct loads,
-// double-buffered.
+// query past S) are exactly 0.  Workgroups per (batch, query head, 256-key
+// tile): 8 waves of 32 keys (K fragments in registers); 64-query Q blocks and
+// their LSE rows stream through LDS by direct loads, double-buffered.  The
+// blocks are independent, so a tile's query blocks are cut into chunks of
+// `chunk`, for about kSavePFillWgs workgroups: with one workgroup per tile, 1024
+// tokens of 32 heads filled half the CUs and took 37.5 us, now 19.7.
 template <int D>
 struct SavePSmem {
   using RT = RowTile<D, NWA>;
@@ -103,7 +107,7 @@ template <int D>
 __global__ void __launch_bounds__(NWA * 64, 2)
 attn_save_p_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ K, int64_t q_stride,
                    int64_t kv_stride, const float* __restrict__ LSE, lt_half* __restrict__ P,
-                   int64_t nblk, int B, int S, int Hq, int Hkv, float scale, int causal) {
+                   int64_t nblk, int chunk, int B, int S, int Hq, int Hkv, float scale, int causal) {
   using SM = SavePSmem<D>;
   using RT = RowTile<D, NWA>;
   constexpr int KK = D / 16;
@@ -121,6 +125,12 @@ attn_save_p_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ K,
   const int kbase = jt * BKV;
   const int kw0 = kbase + wave * 32;
   const int mykey = kw0 + lrow;
+  // this workgroup's query blocks of the tile: it0 .. it_end - 1
+  const int n_qb = (S + BQA - 1) / BQA;
+  const int qb0 = causal ? kbase / BQA : 0;
+  const int it0 = blockIdx.y * chunk;
+  const int it_end = min(it0 + chunk, n_qb - qb0);
+  if (it0 >= it_end) return;                       // uniform: a shorter tile
 
   const lt_half* Kp = K + (int64_t)b * S * kv_stride + (int64_t)kvh * D;
   half8 kf[KK];
@@ -130,9 +140,6 @@ attn_save_p_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ K,
                        : as_half8(u32x4{0, 0, 0, 0});
 
   const float c = scale * kLog2e;
-  const int n_qb = (S + BQA - 1) / BQA;
-  const int qb0 = causal ? kbase / BQA : 0;
-  const int n_iter = n_qb - qb0;
   char* ph = reinterpret_cast<char*>(P) + (int64_t)bh * nblk * kDsBlockBytes + lane * 32;
 
   // Q rows and LSE entries past S read as zero (those queries are masked)
@@ -149,16 +156,16 @@ attn_save_p_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ K,
     }
   };
 
-  if (n_iter > 0) stage(0, 0);
+  stage(it0, it0 & 1);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) loaded_here(kf[kk]);
 
-  for (int it = 0; it < n_iter; ++it) {
+  for (int it = it0; it < it_end; ++it) {
     const int cur = it & 1;
     const int qbase = (n_qb - 1 - it) * BQA;
-    if (it + 1 < n_iter) stage(it + 1, cur ^ 1);
+    if (it + 1 < it_end) stage(it + 1, cur ^ 1);
     const char* qs = smem + cur * SM::TQ;
     const float* lse_s = reinterpret_cast<const float*>(smem + SM::ROW_OFF + cur * 256);
 #pragma unroll
@@ -257,16 +264,19 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
   const int slot = blockIdx.x / (B * Hkv);
   int jt = slot, sp = 0, nsh = 1;                     // key tile, share of its query blocks, shares
   if (nsplit > 1) {
-    const int n_kt = (S + BK - 1) / BK;
-    int lo = 0, hi = n_kt - 1;                        // last tile with off[tile] <= slot
+    // (the table is read as dwords: scalar loads, so that the tile and all
+    // that follows from it stay in scalar registers)
+    const uint32_t* pairs = reinterpret_cast<const uint32_t*>(shares.off);
+    auto off = [&](int j) { return (int)(pairs[j >> 1] >> (16 * (j & 1)) & 0xffffu); };
+    int lo = 0, hi = (S + BK - 1) / BK - 1;           // last tile with off(tile) <= slot
     while (lo < hi) {
       const int mid = (lo + hi + 1) / 2;
-      if (shares.off[mid] <= slot) lo = mid;
+      if (off(mid) <= slot) lo = mid;
       else hi = mid - 1;
     }
-    jt = lo;
-    sp = slot - shares.off[jt];
-    nsh = shares.off[jt + 1] - shares.off[jt];
+    jt = __builtin_amdgcn_readfirstlane(lo);
+    sp = __builtin_amdgcn_readfirstlane(slot - off(jt));
+    nsh = __builtin_amdgcn_readfirstlane(off(jt + 1) - off(jt));
   }
   const int b = bkv / Hkv;
   const int kvh = bkv % Hkv;
@@ -699,18 +709,21 @@ attn_bwd_dkdv_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ 
 }
 
 // ------------------------------------------------------------ kernel 3: dQ from dS
-constexpr int NWQ = 8;          // dQ: waves per workgroup, one 32-query group each
-constexpr int BQQ = NWQ * 32;   // dQ: queries per workgroup
 constexpr int BKQ = 64;         // dQ: keys per slice (two 32-key groups)
-constexpr int NSQ = 3;          // dQ: LDS stages (two slices in flight while one is used)
 
-template <int D>
+// NWQ waves per workgroup, one 32-query group each: 8 (256 queries), or 4
+// where those leave half the CUs without a workgroup (1024 tokens of 32
+// heads: 26.6 us with 8 waves, 24.6 with 4; every workgroup streams K, so more
+// of them than CUs lose: 2048 tokens of 40 heads 47.7 and 57 us).  LDS stages: two slices in flight
+// while one is used, three for the smaller workgroups.
+template <int D, int NWQ>
 struct DqSmem {
   using RT = RowTile<D, NWQ>;
+  static constexpr int NS = NWQ == 8 ? 3 : 4;
   static constexpr int KT = BKQ * RT::ROWB;          // K slice [64][D]
   static constexpr int DSW = 2 * kDsBlockBytes;      // one wave's two dS blocks of a slice
   static constexpr int STAGE = KT + NWQ * DSW;
-  static constexpr int BYTES = NSQ * STAGE;
+  static constexpr int BYTES = NS * STAGE;
   // direct loads per wave and stage: K rows, then always four 1 KiB dS loads
   // (blocks the mask drops load nothing: zero-length buffer), so that the
   // count behind each vmcnt wait is fixed
@@ -741,13 +754,15 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int D>
+template <int D, int NWQ>
 __global__ void __launch_bounds__(NWQ * 64, 1)
 attn_bwd_dq_kernel(const lt_half* __restrict__ K, int64_t kv_stride, const lt_half* __restrict__ ds,
                    int64_t nblk, lt_half* __restrict__ dQ, int64_t dq_stride, int B, int S, int Hq,
                    int Hkv, float scale, int causal) {
-  using SM = DqSmem<D>;
+  using SM = DqSmem<D, NWQ>;
   using RT = RowTile<D, NWQ>;
+  constexpr int BQQ = NWQ * 32;                    // queries per workgroup
+  constexpr int NSQ = SM::NS;
   constexpr int DB = D / 32;
   static_assert(SM::BYTES <= 160 * 1024, "stages fit in LDS");
   __shared__ __attribute__((aligned(1024))) char smem[SM::BYTES];
@@ -795,11 +810,17 @@ attn_bwd_dq_kernel(const lt_half* __restrict__ K, int64_t kv_stride, const lt_ha
     }
   };
 
+  // slices after the next one may stay in flight, up to NSQ - 2 of them
+  auto wait_next = [&](int behind) {
+    if (behind >= NSQ - 2) wait_vmcnt<(NSQ - 2) * SM::LOADS>();
+    else if (NSQ > 3 && behind == 1) wait_vmcnt<SM::LOADS>();
+    else wait_vmcnt<0>();
+  };
   for (int ks = 0; ks < NSQ - 1 && ks < n_ks; ++ks) stage(ks);
-  if (n_ks > 1) wait_vmcnt<SM::LOADS>(); else wait_vmcnt<0>();   // slice 0 resident
+  wait_next(min(NSQ - 1, n_ks) - 1);               // slice 0 resident
   __syncthreads();
   for (int ks = 0; ks < n_ks; ++ks) {
-    // the stage of slice ks + 2 was last read before the previous barrier
+    // the stage of slice ks + NSQ - 1 was last read before the previous barrier
     if (ks + NSQ - 1 < n_ks) stage(ks + NSQ - 1);
     const char* st = smem + (ks % NSQ) * SM::STAGE;
     const char* mine = st + SM::KT + wave * SM::DSW;
@@ -817,9 +838,9 @@ attn_bwd_dq_kernel(const lt_half* __restrict__ K, int64_t kv_stride, const lt_ha
         }
       }
     }
-    // slice ks + 1 resident for every wave (slice ks + 2's loads may still be
+    // slice ks + 1 resident for every wave (later slices' loads may still be
     // in flight); nobody reads stage ks any more
-    if (ks + NSQ - 1 < n_ks) wait_vmcnt<SM::LOADS>(); else wait_vmcnt<0>();
+    wait_next(min(ks + NSQ - 1, n_ks - 1) - (ks + 1));
     __syncthreads();
   }
 
@@ -859,6 +880,8 @@ struct DqrSmem {
 // query groups (128 queries); waves w and w + 4 share a query group and take
 // alternate 32-key blocks of each slice, and their FP32 accumulators are
 // summed through LDS at the end (wave w + 4's into wave w's, fixed order).
+// (64 queries, four waves a group: 39 us against 37 at 1024 tokens of 32
+// heads: the K and V loads per query double.)
 template <int D, int QSPLIT>
 __global__ void __launch_bounds__(NW * 64, 2)
 attn_bwd_dq_recompute_kernel(const lt_half* __restrict__ Q, const lt_half* __restrict__ K,
@@ -1191,20 +1214,30 @@ hipError_t launch_bwd(const AttnBwdArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   // 3. dQ from the stored dS, longest query tiles first
-  const int n_qt = (sh.S + BQQ - 1) / BQQ;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D>), dim3((unsigned)(n_qt * sh.B * sh.Hq)),
-                     dim3(NWQ * 64), 0, s, a.K, a.kv_stride, a.ds, nblk, a.dQ, a.dq_stride, sh.B,
-                     sh.S, sh.Hq, sh.Hkv, sh.scale, sh.causal);
+  auto launch_dq = [&](auto W_) {
+    constexpr int NWQ = decltype(W_)::value;
+    const int n_qt = (sh.S + NWQ * 32 - 1) / (NWQ * 32);
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NWQ>), dim3((unsigned)(n_qt * sh.B * sh.Hq)),
+                       dim3(NWQ * 64), 0, s, a.K, a.kv_stride, a.ds, nblk, a.dQ, a.dq_stride, sh.B,
+                       sh.S, sh.Hq, sh.Hkv, sh.scale, sh.causal);
+  };
+  if ((int64_t)((sh.S + 255) / 256) * sh.B * sh.Hq > kDqHalfWgs) launch_dq(std::integral_constant<int, 8>{});
+  else launch_dq(std::integral_constant<int, 4>{});
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_save_p(const AttnSavePArgs& a, hipStream_t s) {
   const AttnShape& sh = a.sh;
-  const int n_kt = (sh.S + BKV - 1) / BKV;
-  hipLaunchKernelGGL((attn_save_p_kernel<D>), dim3((unsigned)(n_kt * sh.B * sh.Hq)),
+  const int n_kt = (sh.S + BKV - 1) / BKV, n_qb = (sh.S + BQA - 1) / BQA;
+  // blocks per workgroup: two keep the K fragments' load worth it
+  const int64_t blocks = (int64_t)n_kt * sh.B * sh.Hq * n_qb / (sh.causal ? 2 : 1);
+  int64_t chunk = blocks / kSavePFillWgs;
+  chunk = chunk < 2 ? 2 : chunk > n_qb ? n_qb : chunk;
+  hipLaunchKernelGGL((attn_save_p_kernel<D>),
+                     dim3((unsigned)(n_kt * sh.B * sh.Hq), (unsigned)((n_qb + chunk - 1) / chunk)),
                      dim3(NWA * 64), 0, s, a.Q, a.K, a.q_stride, a.kv_stride, a.LSE, a.P,
-                     attn_bwd_ds_blocks(sh.S, sh.causal), sh.B, sh.S, sh.Hq, sh.Hkv, sh.scale,
+                     attn_bwd_ds_blocks(sh.S, sh.causal), (int)chunk, sh.B, sh.S, sh.Hq, sh.Hkv, sh.scale,
                      sh.causal);
   return hipGetLastError();
 }
@@ -1214,20 +1247,16 @@ hipError_t launch_save_p(const AttnSavePArgs& a, hipStream_t s) {
 template <int D>
 hipError_t launch_bwd_p(const AttnBwdArgs& a, hipStream_t s) {
   const AttnShape& sh = a.sh;
-  const int64_t wgs256 = (int64_t)((sh.S + BQB - 1) / BQB) * sh.B * sh.Hq;
-  if (wgs256 >= kDqFillWgs) {
-    const int n_qt = (sh.S + BQB - 1) / BQB;
-    hipLaunchKernelGGL((attn_bwd_dq_recompute_kernel<D, 1>), dim3((unsigned)(n_qt * sh.B * sh.Hq)),
+  auto launch_dq = [&](auto Q_) {
+    constexpr int QS = decltype(Q_)::value;
+    const int n_qt = (sh.S + BQB / QS - 1) / (BQB / QS);
+    hipLaunchKernelGGL((attn_bwd_dq_recompute_kernel<D, QS>), dim3((unsigned)(n_qt * sh.B * sh.Hq)),
                        dim3(NW * 64), 0, s, a.Q, a.K, a.V, a.q_stride, a.kv_stride, a.O, a.dO,
                        a.o_stride, a.LSE, a.lse2, a.delta, a.dQ, a.dq_stride, sh.B, sh.S, sh.Hq,
                        sh.Hkv, sh.scale, sh.causal);
-  } else {
-    const int n_qt = (sh.S + BQB / 2 - 1) / (BQB / 2);
-    hipLaunchKernelGGL((attn_bwd_dq_recompute_kernel<D, 2>), dim3((unsigned)(n_qt * sh.B * sh.Hq)),
-                       dim3(NW * 64), 0, s, a.Q, a.K, a.V, a.q_stride, a.kv_stride, a.O, a.dO,
-                       a.o_stride, a.LSE, a.lse2, a.delta, a.dQ, a.dq_stride, sh.B, sh.S, sh.Hq,
-                       sh.Hkv, sh.scale, sh.causal);
-  }
+  };
+  if ((int64_t)((sh.S + BQB - 1) / BQB) * sh.B * sh.Hq >= kDqFillWgs) launch_dq(std::integral_constant<int, 1>{});
+  else launch_dq(std::integral_constant<int, 2>{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nblk = attn_bwd_ds_blocks(sh.S, sh.causal);

@@ -97,7 +97,7 @@ struct AttnFwdArgs {
 constexpr int kMaxSplitTiles = 512;   // a split has tiles x B x Hkv < 512
 struct DkdvShares {
   int m;
-  uint16_t off[kMaxSplitTiles + 1];
+  uint16_t off[kMaxSplitTiles + 2];   // (an even count: read in pairs)
 };
 
 struct AttnBwdArgs {
@@ -198,15 +198,16 @@ inline size_t attn_bwd_part_bytes(int B, int S, int Hq, int Hkv, int D) {
   return n > 1 ? align256((size_t)2 * n * B * S * Hkv * D * sizeof(float)) : 0;
 }
 
-// Shares per key tile: enough for one to four rounds of workgroups (one per
-// CU), in proportion to the tiles' work -- under the causal mask the first
-// tile has many times the last one's, and equal shares leave the CUs waiting
-// for its workgroups -- within the workspace's rows for nsplit equal shares.
-// Returns false where one workgroup per tile is estimated no slower (no
-// partials and no sum pass then).
-//   Equal shares of one query head each, 2048 tokens of 40:8 heads: 320
-//   workgroups of 32 .. 4 blocks for 256 CUs, dK/dV pass 122 us; 256 of at
-//   most 25 blocks: 97 us.
+// Shares per key tile, chosen by estimated time within the workspace's rows for
+// nsplit equal shares.  Candidates: one workgroup per tile (no partials and no
+// sum pass: returns false); nsplit shares of every tile; and shares in
+// proportion to the tiles' work for one to four rounds of workgroups (one per
+// CU) -- under the causal mask the first tile has many times the last one's
+// work, and equal shares leave the CUs waiting for its workgroups.
+//   2048 tokens of 40:8 heads, equal shares of one query head: 320 workgroups
+//   of 32 .. 4 blocks, 122 us; 256 of at most 25 blocks: 107 us.  4096
+//   tokens: 640 equal shares balance by themselves and keep the key tiles of
+//   a head on the same Q / dO blocks: whole backward 650 us, proportional 670.
 inline bool attn_bwd_shares(int B, int S, int Hq, int Hkv, int D, int causal, const DkdvPlan& plan,
                             DkdvShares* out) {
   constexpr int64_t kCUs = 256;
@@ -218,35 +219,58 @@ inline bool attn_bwd_shares(int B, int S, int Hq, int Hkv, int D, int causal, co
   const int64_t slots_max = n_kt == 1 ? plan.nsplit : (int64_t)plan.nsplit * S / plan.ktile;
   int64_t total = 0;
   for (int j = 0; j < n_kt; ++j) total += work(j);
+  // us of the pass with m slots a head, the longest of c blocks: a 64-query
+  // block of a 256-key tile takes 4.3 us at D = 128 (15% more where the
+  // shares cut through query heads), a workgroup's start and end about 10,
+  // with partials 20; the sum pass streams those at about 6 TB/s
+  const double size = (double)plan.ktile / 256 * D / 128;
+  auto cost = [&](int64_t c, int64_t m, bool whole) {
+    const double rounds = (double)(m * heads) / kCUs;
+    const double avg = 1.08 * (double)(total * heads) / kCUs;
+    const double blocks = rounds > 1.0 && avg > (double)c ? avg : (double)c;
+    const double us = blocks * 4.3 * size * (whole ? 1.0 : 1.15);
+    const double ends = (m > n_kt ? 20.0 : 10.0) * size * (rounds > 1.0 ? rounds : 1.0);
+    return us + ends + (m > n_kt ? 4.0 + (double)(m * heads) * plan.ktile * D * 8 / 6.0e6 : 0.0);
+  };
+  // equal shares, as far as the rows go: a ragged last tile gets fewer
+  int64_t last = n_kt == 1 ? plan.nsplit : slots_max - (n_kt - 1) * (int64_t)plan.nsplit;
+  const int64_t less = last < 1 ? 1 : 0;             // ... and its neighbour one less
+  if (last < 1) last = 1;
+  if (last > work(n_kt - 1)) last = work(n_kt - 1);
+  auto equal = [&](int j) {
+    const int64_t n = j == n_kt - 1 ? last : j == n_kt - 2 ? plan.nsplit - less : plan.nsplit;
+    return n < work(j) ? n : work(j);
+  };
+  int64_t eq_m = 0, eq_c = 0;
+  for (int j = 0; j < n_kt; ++j) {
+    const int64_t c = (work(j) + equal(j) - 1) / equal(j);
+    eq_m += equal(j);
+    if (c > eq_c) eq_c = c;
+  }
   // slots with no workgroup above c blocks
   auto slots = [&](int64_t c) {
     int64_t m = 0;
     for (int j = 0; j < n_kt; ++j) m += (work(j) + c - 1) / c;
     return m;
   };
-  // us of the pass: a 64-query block of a 256-key tile takes 5.7 us at D =
-  // 128, starting and ending a workgroup about 6; the sum pass streams the
-  // partials at about 6 TB/s
-  auto cost = [&](int64_t c, int64_t m) {
-    const int64_t wgs = m * heads, rounds = (wgs + kCUs - 1) / kCUs;
-    const double avg = (double)(total * heads) / kCUs, longest = (double)c;
-    const double blocks = rounds == 1 ? longest : (avg > longest ? avg : longest) + 0.35 * longest;
-    const double us = blocks * (D == 128 ? 5.7 : 3.5) * plan.ktile / 256 + 6.0 * (double)rounds;
-    return m == n_kt ? us : us + 4.0 + (double)wgs * plan.ktile * D * 8 / 6.0e6;
-  };
-  int64_t best_c = work(0);
-  double best = cost(best_c, n_kt);
+  int64_t best_c = work(0);                          // 0: equal shares
+  double best = cost(best_c, n_kt, true);
+  const double eq_us = cost(eq_c, eq_m, grp % plan.nsplit == 0);
+  if (eq_m > n_kt && eq_us < best) {
+    best = eq_us;
+    best_c = 0;
+  }
   for (int64_t r = 1; r <= 4; ++r) {
     int64_t m = r * kCUs / heads;
     if (m > slots_max) m = slots_max;
     if (m <= n_kt) continue;
-    int64_t lo = 1, hi = work(0);      // smallest c with slots(c) <= m
+    int64_t lo = 1, hi = work(0);                    // smallest c with slots(c) <= m
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
       if (slots(mid) <= m) hi = mid;
       else lo = mid + 1;
     }
-    const double us = cost(lo, slots(lo));
+    const double us = cost(lo, slots(lo), false);
     if (us < best) {
       best = us;
       best_c = lo;
@@ -255,7 +279,7 @@ inline bool attn_bwd_shares(int B, int S, int Hq, int Hkv, int D, int causal, co
   int64_t m = 0;
   for (int j = 0; j < n_kt; ++j) {
     out->off[j] = (uint16_t)m;
-    m += (work(j) + best_c - 1) / best_c;
+    m += best_c ? (work(j) + best_c - 1) / best_c : equal(j);
   }
   out->off[n_kt] = (uint16_t)m;
   out->m = (int)m;
