@@ -155,9 +155,14 @@ def _ptr(x):
 
 def _stream(stream):
     if stream is None:
-        import torch
-        if torch.cuda.is_available():
-            return torch.cuda.current_stream().cuda_stream
+        # once torch's HIP state exists, its current stream is two C calls;
+        # torch.cuda.is_available() and a Stream object cost more host time
+        # than the launch of a small kernel takes on the GPU
+        if torch is not None and torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        import torch as _torch
+        if _torch.cuda.is_available():
+            return _torch.cuda.current_stream().cuda_stream
         return None
     if isinstance(stream, int):
         return stream
