@@ -79,18 +79,26 @@ rmsnorm_fwd_kernel(const lt_half* __restrict__ X, int64_t ldx, const lt_half* __
 // row's dot product goes through the waves (one barrier a row, sums in wave
 // order).  With one wave per row a row's 30 KB were loaded, reduced and
 // written in turn by 8 waves a CU: 4096 x 5120 took 52 us (3.2 TB/s), now 41.
+// Narrow rows would leave lanes idle: up to 512 (1024) columns a row takes one
+// (two) of the four waves, the groups take rows side by side and add their dw
+// partials through LDS at the end.
 constexpr int kBwdWaves = kRmsBwdWaves;
 constexpr int kBwdThreads = 64 * kBwdWaves;
 
-template <int KPT>
+// KPT chunks per thread, WR waves per row
+template <int KPT, int WR>
 __global__ void __launch_bounds__(kBwdThreads)
 rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* __restrict__ X,
                    int64_t ldx, const lt_half* __restrict__ W, const float* __restrict__ RSTD,
                    const lt_half* __restrict__ R, int64_t ldr, lt_half* __restrict__ dX,
                    int64_t lddx, float* __restrict__ part, int64_t T, int H) {
+  constexpr int GT = 64 * WR;                      // threads of a row group
+  constexpr int NG = kBwdWaves / WR;               // row groups
+  static_assert(NG == 1 || KPT == 1, "groups: rows of one chunk per thread");
   __shared__ float red[2][kBwdWaves];
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
+  const int wave = threadIdx.x >> 6;
+  const int grp = wave / WR;
+  const int tid = threadIdx.x % GT;                // within the row group
   const int nch = H / 8;
   const float inv_h = 1.f / (float)H;
   const u32x4 zero = {0, 0, 0, 0};
@@ -99,7 +107,7 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
   float dw[KPT][8];
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
-    const int c = tid + kBwdThreads * k;
+    const int c = tid + GT * k;
     wv[k] = as_half8(c < nch ? ld16(W + c * 8) : zero);
 #pragma unroll
     for (int e = 0; e < 8; ++e) dw[k][e] = 0.f;
@@ -113,7 +121,7 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
     v.rstd = RSTD[row];
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
-      const int c = tid + kBwdThreads * k;
+      const int c = tid + GT * k;
       v.g[k] = v.x[k] = v.r[k] = as_half8(zero);
       if (c < nch) {
         v.g[k] = as_half8(ld16(dY + row * lddy + c * 8));
@@ -130,16 +138,19 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
 #pragma unroll
       for (int e = 0; e < 8; ++e) dot += (float)v.g[k][e] * (float)wv[k][e] * (float)v.x[k][e];
     dot = wave_sum(dot);
-    if ((tid & 63) == 0) red[buf][wave] = dot;
-    __syncthreads();
-    float sum = 0.f;
+    float sum = dot;
+    if constexpr (WR > 1) {
+      if ((tid & 63) == 0) red[buf][wave] = dot;
+      __syncthreads();
+      sum = 0.f;
 #pragma unroll
-    for (int q = 0; q < kBwdWaves; ++q) sum += red[buf][q];
+      for (int q = 0; q < WR; ++q) sum += red[buf][grp * WR + q];
+    }
     const float r = v.rstd;
     const float c3 = r * r * r * sum * inv_h;
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
-      const int c = tid + kBwdThreads * k;
+      const int c = tid + GT * k;
       half8 o;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -147,7 +158,7 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
         dw[k][e] += g * x * r;
         o[e] = (_Float16)((float)v.r[k][e] + (r * (float)wv[k][e] * g - c3 * x));
       }
-      if (c < nch) st16(dX + row * lddx + c * 8, as_u32x4(o));
+      if (c < nch && (NG == 1 || row < T)) st16(dX + row * lddx + c * 8, as_u32x4(o));
     }
   };
 
@@ -155,23 +166,49 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
   // (a contiguous range each: 43 us against 41 at 4096 x 5120; a third row in
   // flight changes nothing).  Two rows per trip: two register sets, two reduction slots (a slot is written
   // again only after the barrier of the row between).
-  const int64_t step = gridDim.x;
-  if (blockIdx.x < T) {
-    Row a, b;
-    load(blockIdx.x, a);
-    for (int64_t row = blockIdx.x; row < T; row += 2 * step) {
-      if (row + step < T) load(row + step, b);
-      finish(row, a, 0);
-      if (row + step >= T) break;
-      if (row + 2 * step < T) load(row + 2 * step, a);
-      finish(row + step, b, 1);
+  // Groups run the same number of steps (barriers inside); a group without a
+  // row left repeats its last one with nothing stored and zero g.
+  const int64_t step = (int64_t)gridDim.x * NG;
+  const int64_t first = (int64_t)blockIdx.x * NG;
+  auto load_row = [&](int64_t base, Row& v) __attribute__((always_inline)) {
+    const int64_t row = base + grp;
+    load(row < T ? row : T - 1, v);
+    if (NG > 1 && row >= T) {
+#pragma unroll
+      for (int k = 0; k < KPT; ++k) v.g[k] = as_half8(zero);
     }
+  };
+  if (first < T) {
+    Row a, b;
+    load_row(first, a);
+    for (int64_t row = first; row < T; row += 2 * step) {
+      if (row + step < T) load_row(row + step, b);
+      finish(row + grp, a, 0);
+      if (row + step >= T) break;
+      if (row + 2 * step < T) load_row(row + 2 * step, a);
+      finish(row + step + grp, b, 1);
+    }
+  }
+
+  if constexpr (NG > 1) {
+    // the other groups' partials, added in group order by the first
+    __shared__ float acc[NG - 1][GT * 8];
+    if (grp > 0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[grp - 1][tid * 8 + e] = dw[0][e];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g = 0; g < NG - 1; ++g)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dw[0][e] += acc[g][tid * 8 + e];
   }
 
   float* dst = part + (int64_t)blockIdx.x * H;
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
-    const int c = tid + kBwdThreads * k;
+    const int c = tid + GT * k;
     if (c < nch) {
       *reinterpret_cast<float4*>(dst + c * 8) = make_float4(dw[k][0], dw[k][1], dw[k][2], dw[k][3]);
       *reinterpret_cast<float4*>(dst + c * 8 + 4) = make_float4(dw[k][4], dw[k][5], dw[k][6], dw[k][7]);
@@ -276,10 +313,10 @@ hipError_t launch_rms_fwd(const lt_half* X, int64_t ldx, const lt_half* W, lt_ha
   return hipGetLastError();
 }
 
-template <int KPT>
+template <int KPT, int WR>
 hipError_t launch_rms_bwd(const RmsBwdArgs& a, hipStream_t s) {
   const int nblk = rmsnorm_bwd_blocks(a.T);
-  hipLaunchKernelGGL((rmsnorm_bwd_kernel<KPT>), dim3((unsigned)nblk), dim3(kBwdThreads), 0, s,
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<KPT, WR>), dim3((unsigned)nblk), dim3(kBwdThreads), 0, s,
                      a.dY, a.lddy, a.X, a.ldx, a.W, a.RSTD, a.R, a.ldr, a.dX, a.lddx, a.part, a.T,
                      (int)a.H);
   hipError_t e = hipGetLastError();
@@ -302,11 +339,14 @@ hipError_t rmsnorm_fwd_launch(const lt_half* X, int64_t ldx, const lt_half* W, l
 }
 
 hipError_t rmsnorm_bwd_launch(const RmsBwdArgs& a, hipStream_t s) {
-  switch ((a.H / 8 + kBwdThreads - 1) / kBwdThreads) {   // chunks per thread: H <= 8192
-    case 1: return launch_rms_bwd<1>(a, s);
-    case 2: return launch_rms_bwd<2>(a, s);
-    case 3: return launch_rms_bwd<3>(a, s);
-    default: return launch_rms_bwd<4>(a, s);
+  const int64_t nch = a.H / 8;
+  if (nch <= 64) return launch_rms_bwd<1, 1>(a, s);
+  if (nch <= 128) return launch_rms_bwd<1, 2>(a, s);
+  switch ((nch + kBwdThreads - 1) / kBwdThreads) {   // chunks per thread: H <= 8192
+    case 1: return launch_rms_bwd<1, 4>(a, s);
+    case 2: return launch_rms_bwd<2, 4>(a, s);
+    case 3: return launch_rms_bwd<3, 4>(a, s);
+    default: return launch_rms_bwd<4, 4>(a, s);
   }
 }
 
