@@ -6,22 +6,22 @@
 // (DDR -> GSM -> SM / AM staging, VLIW micro-kernel) is replaced here by the
 // CDNA4 form of the same idea:
 //   * a workgroup owns a BM x BN output tile held in MFMA accumulators
-//     (16x16x32 FP16 MFMA, FP32 accumulate).  256x256 tiles of the forward
-//     and data-gradient layouts use 4 waves, one per SIMD, each a 128x128
-//     wave tile with its accumulators in AGPRs; their main loop is a fixed
-//     sequence of asm statements (fragment reads a whole k-step ahead, MFMAs,
-//     direct loads, counter waits), so that one wave keeps its matrix unit
-//     fed without a second wave to cover its waits.  Every layout and the
-//     split-K partial tiles use it; the half-size tail tiles and the
-//     ragged-K form use 8 waves, two per SIMD, whose compiler-scheduled loop
-//     relies on the other wave to cover LDS and barrier waits;
-//   * K is walked in 64-wide slices, double-buffered in LDS.  Operands move
-//     HBM -> LDS with direct buffer loads (16 B per lane, no register
-//     staging), issued one slice ahead so that they overlap the current
-//     slice's MFMA work -- the overlap of operand preparation with MACs that
-//     the paper's micro-kernel pipeline provides.  In 8-wave tiles only one
-//     wave per SIMD issues them ("loader waves"), with uniform (scalar)
-//     addressing;
+//     (16x16x32 FP16 MFMA, FP32 accumulate).  256x256, 256x128, 128x256,
+//     128x128 and 64x64 tiles use 4 waves, one per SIMD, in a 2x2 grid with
+//     their accumulators in AGPRs; their main loop is a fixed sequence of asm
+//     statements (fragment reads a whole k-step ahead, MFMAs, direct loads,
+//     counter waits), so that one wave keeps its matrix unit fed without a
+//     second wave to cover its waits.  Every layout, the fused epilogues and
+//     the split-K partial tiles use it; only the ragged-K form of layouts with
+//     a K-contiguous operand uses compiler-scheduled loops (8 waves, two per
+//     SIMD, at 256x256: the other wave covers LDS and barrier waits);
+//   * K is walked in 64-wide slices, in two LDS stages at 256x256 and up to
+//     eight at smaller tiles.  Operands move HBM -> LDS with direct buffer
+//     loads (16 B per lane, no register staging), issued one or more slices
+//     ahead so that they overlap the current slice's MFMA work -- the
+//     overlap of operand preparation with MACs that the paper's micro-kernel
+//     pipeline provides.  In 8-wave tiles only one wave per SIMD issues them
+//     ("loader waves"), with uniform (scalar) addressing;
 //   * each operand keeps its HBM orientation in LDS.  A K-contiguous operand
 //     (forward A and B, dgrad A) is stored row-major; an M/N-contiguous one
 //     (dgrad B, wgrad A and B) is stored k-major and read with the gfx950
@@ -34,14 +34,14 @@
 //     grouped eight tile-rows at a time for L2 reuse of A and B.
 //   Buffer loads return zeros out of range, which provides the M, N and K
 //   tails without branches.
-//   A last wave of 256x256 tiles at most half full runs either as half-size
-//   tiles (256x128 / 128x256) or, when the caller provides an FP32 workspace,
-//   as 256x256 tiles whose K is split over several workgroups (epilogue 3
-//   stores their partial sums; splitk_reduce_kernel adds them in a fixed
-//   order and applies alpha, beta * R and the bias).  With a workspace, a
-//   launch of less than about one wave of 256x256 tiles is split the same
-//   way as a whole when the split gives twice the workgroups of 128x128 tiles
-//   or keeps a long K loop per split; else it runs as 128x128 tiles.
+//   * results leave through LDS, 16 rows of a wave at a time, so that memory
+//     sees whole lines (see the epilogue).
+//   gemm_plan chooses the launch: one tile size, or whole rounds of 256x256
+//   tiles and a tail of smaller ones, or, when the caller provides an FP32
+//   workspace, a tail (or the whole product) of 256x256 tiles whose K is split
+//   over several workgroups (epilogue 3 stores their partial sums;
+//   splitk_reduce_kernel adds them in a fixed order and applies alpha,
+//   beta * R and the bias).
 #include <type_traits>
 #include <utility>
 

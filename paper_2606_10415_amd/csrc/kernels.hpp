@@ -35,8 +35,9 @@ struct GemmArgs {
   // gate/up epilogues: distance between gate and up rows of B (1) / columns
   // of C and X1 (1, 2); 0 means F (set for launches over part of the columns)
   int64_t pair_off = 0;
-  // optional FP32 workspace (epilogue 0): a last wave at most half full then
-  // runs with its K split (gemm_splitk_tail), when ws_bytes suffices
+  // optional FP32 workspace (epilogue 0): the plan may then split the K of a
+  // last wave at most half full, or of a launch under one wave
+  // (gemm_splitk_tail), when ws_bytes suffices
   float* ws = nullptr;
   size_t ws_bytes = 0;
 };
