@@ -66,7 +66,7 @@ __device__ __forceinline__ void lds_dma16_stream(const void* base, uint32_t nrec
   r[2] = __builtin_amdgcn_readfirstlane(nrec);
   r[3] = 0x00020000u;
   const uint32_t m0v = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                :
                : "s"(m0v), "v"(voff), "s"(r)
                : "memory");

@@ -290,10 +290,11 @@ __device__ __forceinline__ void sfor(F&& f) {
   sfor_impl(std::make_integer_sequence<int, N>{}, f);
 }
 // direct 16-byte-per-lane load into LDS at m0 = mbase + OFF (uniform); the
-// addition sets SCC, which may otherwise hold a loop condition or a carry
+// addition sets SCC, which may otherwise hold a loop condition or a carry; the
+// s_nop is the wait state between a write of M0 and a load into LDS
 template <int OFF>
 __device__ __forceinline__ void dma16_at(uint32_t mbase, uint32_t voff, u32x4 desc) {
-  asm volatile("s_add_u32 m0, %0, %3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :
                : "s"(mbase), "v"(voff), "s"(desc), "n"(OFF)
                : "memory", "scc");

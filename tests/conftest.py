@@ -1,8 +1,11 @@
+import functools
 import json
 import math
 import os
 import re
+import subprocess
 import sys
+import tempfile
 
 import numpy as np
 import pytest
@@ -17,6 +20,21 @@ GOLDEN = os.path.join(ROOT, "tests", "golden")
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (gfx950) GPU and the built HIP library")
     config.addinivalue_line("markers", "slow: full-size parity case (minutes of oracle time)")
+
+
+@functools.lru_cache(maxsize=None)
+def device_asm(source):
+    """Lines of the gfx950 assembly of csrc/<source>, compiled once per run with
+    the build's flags (needs no GPU); skips where hipcc is missing."""
+    from paper_2606_10415_amd import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not available")
+    with tempfile.TemporaryDirectory() as d:
+        out = os.path.join(d, "device.s")
+        subprocess.run([build.HIPCC, *build.COMMON_FLAGS, "--cuda-device-only", "-S", "-x", "hip",
+                        os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
+        with open(out) as f:
+            return f.read().split("\n")
 
 
 def load_golden(name):

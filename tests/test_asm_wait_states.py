@@ -1,0 +1,112 @@
+"""Wait states around the asm direct loads, on the kernels' gfx950 assembly.
+
+The compiler inserts the wait states that the hardware does not interlock, but
+only between instructions of its own: what an asm statement holds, and the
+instructions just before it, are outside its checks.  The direct loads into
+LDS are such statements:
+
+  * a load into LDS reads m0, and needs one wait state after a scalar
+    instruction has written it.
+
+An instruction counts as one wait state, `s_nop n` as n + 1; distances are
+taken over every control-flow path.
+"""
+
+import collections
+import re
+
+import pytest
+
+from conftest import device_asm
+
+SOURCES = ["gemm_f16.hip", "attn_fwd.hip", "attn_bwd.hip"]
+
+
+def functions(lines):
+    """name -> {label: [instructions]} in program order"""
+    out, blocks = {}, None
+    for line in lines:
+        m = re.match(r"^(_Z\S+):", line)
+        if m:
+            blocks = out[m.group(1)] = collections.OrderedDict(entry=[])
+            cur = "entry"
+            continue
+        if blocks is None:
+            continue
+        if line.startswith(".Lfunc_end"):
+            blocks = None
+            continue
+        m = re.match(r"^(\.LBB\d+_\d+):", line)
+        if m:
+            cur = m.group(1)
+            blocks[cur] = []
+            continue
+        t = line.split(";")[0].strip()
+        if t and not t.startswith((".", "#")):
+            blocks[cur].append(t)
+    return out
+
+
+def predecessors(blocks):
+    pred, names = collections.defaultdict(list), list(blocks)
+    for k, b in enumerate(names):
+        ins = blocks[b]
+        succ = [t.split()[1] for t in ins if t.startswith(("s_cbranch", "s_branch"))]
+        if not (ins and ins[-1].startswith(("s_branch", "s_endpgm", "s_setpc"))) and k + 1 < len(names):
+            succ.append(names[k + 1])
+        for s in succ:
+            pred[s].append(b)
+    return pred
+
+
+def waits_since(blocks, pred, label, index, need, hit):
+    """Fewest wait states between instruction (label, index) and an earlier one
+    that `hit` accepts, over all paths; None if there are `need` or more."""
+    work, best, seen = [(label, index - 1, 0)], None, {}
+    while work:
+        b, j, w = work.pop()
+        while j >= 0 and w < need:
+            t = blocks[b][j]
+            if hit(t):
+                best = w if best is None else min(best, w)
+                break
+            m = re.match(r"s_nop (\d+)", t)
+            w += int(m.group(1)) + 1 if m else 1
+            j -= 1
+        else:
+            if w < need:
+                for p in pred[b]:
+                    if seen.get(p, need) > w:
+                        seen[p] = w
+                        work.append((p, len(blocks[p]) - 1, w))
+    return best
+
+
+def lds_loads(blocks):
+    return [(b, i) for b, ins in blocks.items() for i, t in enumerate(ins)
+            if t.startswith("buffer_load") and t.endswith(" lds")]
+
+
+def early_m0(blocks):
+    """Loads into LDS less than one wait state behind a write of m0."""
+    pred = predecessors(blocks)
+    return [(b, blocks[b][max(0, i - 2):i + 1]) for b, i in lds_loads(blocks)
+            if waits_since(blocks, pred, b, i, 1, lambda t: re.match(r"s_\w+ m0\b", t)) is not None]
+
+
+LOAD = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
+
+
+def test_checker_finds_an_early_m0():
+    assert early_m0({"entry": ["s_mov_b32 m0, s1", LOAD]})
+    assert not early_m0({"entry": ["s_mov_b32 m0, s1", "s_nop 0", LOAD]})
+    # over a branch
+    assert early_m0({"entry": ["s_add_u32 m0, s1, 64"], ".LBB0_1": [LOAD, "s_cbranch_scc1 .LBB0_1"]})
+
+
+@pytest.mark.parametrize("source", SOURCES)
+def test_m0_is_settled_before_a_load_into_lds(source):
+    kernels = functions(device_asm(source))
+    assert sum(len(lds_loads(b)) for b in kernels.values()) > 50
+    bad = [(name[:80], x) for name, blocks in kernels.items() for x in early_m0(blocks)]
+    assert not bad, (len(bad), bad[:3])
