@@ -111,8 +111,11 @@ struct Operand {
       }
     } else if constexpr (KC) {
       // rows past the matrix fall outside the buffer and read as zero
-      const int64_t nvalid = rows - row0 < R ? rows - row0 : R;
-      nrec = (uint32_t)(nvalid * ld * 2);
+      // (32-bit sums: the scalar unit has no 64-bit compare, and a range
+      // held in a vector register would reach the descriptor through a
+      // v_readfirstlane, whose result the asm loads may not use at once)
+      const int left = (int)rows - (int)row0;
+      nrec = __builtin_amdgcn_readfirstlane((uint32_t)(left < R ? left : R) * (uint32_t)ld * 2);
 #pragma unroll
       for (int t = 0; t < PERW; ++t) {
         const int r = (wave * PERW + t) * RPI + lane / CPR;
@@ -186,21 +189,21 @@ struct Operand {
 
   // one direct load (index t of this wave's PERW) of the K-contiguous slice
   // at k0 with kv = clamp(K - k0, 0, BK) valid columns; kv = 0 fills the
-  // tile with zeros and touches no memory (empty range)
+  // tile with zeros and touches no memory (every offset out of range)
   __device__ __forceinline__ void load1(char* lds, int64_t k0, int kv, int t, int wave,
                                         int lane) const {
     const int i = wave * PERW + t;
+    const int64_t kb = kv > 0 ? k0 : 0;
     if constexpr (KC) {
-      const lt_half* b = PAIRED ? base + (kv > 0 ? k0 : 0) : base + row0 * ld + (kv > 0 ? k0 : 0);
-      const uint32_t n = kv > 0 ? (PAIRED ? nrec : nrec - (uint32_t)(k0 * 2)) : 0u;
+      const lt_half* b = PAIRED ? base + kb : base + row0 * ld + kb;
+      const uint32_t n = PAIRED ? nrec : nrec - (uint32_t)(kb * 2);
       const int r = i * RPI + lane / CPR;
       const uint32_t off = ((lane % CPR) ^ swz(r)) * 8 >= kv ? kOOB : voff[t];
       lds_dma16_opaque(b, n, lds + i * 1024, off);
     } else {
-      const lt_half* b = base + (kv > 0 ? k0 * ld : 0) + row0;
-      const uint32_t n = kv > 0 ? nrec : 0u;
+      const lt_half* b = base + kb * ld + row0;
       const uint32_t off = i * KR_PER + lane / LPR >= kv ? kOOB : voff[t];
-      lds_dma16_opaque(b, n, lds + i * 1024, off);
+      lds_dma16_opaque(b, nrec, lds + i * 1024, off);
     }
   }
 
@@ -421,12 +424,12 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
 
   OA oa;
   OB ob;
-  const bool loader = wave < LOADERS;
-  if (loader) oa.init(A, lda, m0, M, wave, lane);
-  if constexpr (EPI == 1)
-    { if (loader) ob.init(B, ldb, n0, Fb, wave, lane, P); }
-  else
-    { if (loader) ob.init(B, ldb, n0, N, wave, lane); }
+  // (waves that load nothing set their operands up too: behind a branch the
+  // buffer ranges would not stay in scalar registers)
+  const bool loader = !SPLIT_ISSUE || wave < LOADERS;
+  oa.init(A, lda, m0, M, wave, lane);
+  if constexpr (EPI == 1) ob.init(B, ldb, n0, Fb, wave, lane, P);
+  else ob.init(B, ldb, n0, N, wave, lane);
 
   f32x4 acc[TM][TN];
 #pragma unroll
@@ -437,9 +440,10 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
   const int nk = (int)((K + BK - 1) / BK);
+  // (K is at most 2^30: 32-bit sums stay in scalar registers, as in init)
   auto kvalid = [&](int kt) {
-    const int64_t rem = K - (int64_t)kt * BK;
-    return rem >= BK ? BK : (int)rem;
+    const int rem = (int)K - kt * BK;
+    return rem >= BK ? BK : rem;
   };
   auto stage_of = [&](int kt) { return smem + (kt % NS) * STAGE; };
   auto issue = [&](int kt) {
@@ -588,8 +592,8 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
     // prologue: slices 0 .. NS-1 in flight (those past K fill their stage
     // with zeros), slice 0 resident, its first k-step's fragments into set 0
     auto kv_of = [&](int kt) {
-      const int64_t rem = K - (int64_t)kt * BK;
-      return rem >= BK ? BK : rem > 0 ? (int)rem : 0;
+      const int rem = (int)K - kt * BK;
+      return rem >= BK ? BK : rem > 0 ? rem : 0;
     };
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {

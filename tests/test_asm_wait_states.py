@@ -6,7 +6,11 @@ instructions just before it, are outside its checks.  The direct loads into
 LDS are such statements:
 
   * a load into LDS reads m0, and needs one wait state after a scalar
-    instruction has written it.
+    instruction has written it;
+  * a buffer or global access needs five wait states after a vector
+    instruction (v_readfirstlane, a compare, a spill's v_readlane) has written
+    a scalar register that it reads, here a word of the buffer descriptor.  A
+    load with an old range would drop rows, or read past the matrix.
 
 An instruction counts as one wait state, `s_nop n` as n + 1; distances are
 taken over every control-flow path.
@@ -94,6 +98,41 @@ def early_m0(blocks):
             if waits_since(blocks, pred, b, i, 1, lambda t: re.match(r"s_\w+ m0\b", t)) is not None]
 
 
+def scalars(token):
+    token = token.strip()
+    if token == "vcc":
+        return {"vcc_lo", "vcc_hi"}
+    m = re.match(r"s\[(\d+):(\d+)\]$", token)
+    if m:
+        return {f"s{i}" for i in range(int(m.group(1)), int(m.group(2)) + 1)}
+    return {token} if re.match(r"(s\d+|vcc_lo|vcc_hi|m0)$", token) else set()
+
+
+def vector_written_scalars(t):
+    """Scalar registers that a vector instruction writes."""
+    op, _, rest = t.partition(" ")
+    args = rest.split(",")
+    if op.startswith(("v_readfirstlane", "v_readlane", "v_cmp")):
+        return scalars(args[0])
+    if op.startswith(("v_add_co", "v_sub_co", "v_addc_co", "v_subb_co", "v_subrev_co", "v_subbrev_co", "v_div_scale",
+                      "v_mad_u64_u32", "v_mad_i64_i32")):
+        return scalars(args[1])
+    return set()
+
+
+def early_scalars(blocks):
+    """Memory accesses less than five wait states behind a vector write of one of their scalars."""
+    pred, bad = predecessors(blocks), []
+    for b, ins in blocks.items():
+        for i, t in enumerate(ins):
+            if not t.startswith(("buffer_", "global_", "flat_", "scratch_")):
+                continue
+            reads = set().union(*(scalars(w) for x in t.split(",") for w in x.split()))
+            if reads and waits_since(blocks, pred, b, i, 5, lambda x: vector_written_scalars(x) & reads) is not None:
+                bad.append((b, ins[max(0, i - 6):i + 1]))
+    return bad
+
+
 LOAD = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
 
 
@@ -104,9 +143,25 @@ def test_checker_finds_an_early_m0():
     assert early_m0({"entry": ["s_add_u32 m0, s1, 64"], ".LBB0_1": [LOAD, "s_cbranch_scc1 .LBB0_1"]})
 
 
+def test_checker_finds_an_early_descriptor_word():
+    wait = ["s_nop 0", "s_mov_b32 m0, s1", "s_nop 0"]
+    assert early_scalars({"entry": ["v_readfirstlane_b32 s6, v2", *wait, LOAD]})
+    assert early_scalars({"entry": ["v_readlane_b32 s4, v2, 3", *wait], ".LBB0_1": ["s_nop 0", LOAD]})
+    assert not early_scalars({"entry": ["v_readfirstlane_b32 s6, v2", *wait, "s_nop 1", LOAD]})
+    assert not early_scalars({"entry": ["v_readfirstlane_b32 s8, v2", LOAD]})
+    assert not early_scalars({"entry": ["v_readfirstlane_b32 s9, v2", "s_mov_b32 s6, s9", "s_nop 0", LOAD]})
+
+
 @pytest.mark.parametrize("source", SOURCES)
 def test_m0_is_settled_before_a_load_into_lds(source):
     kernels = functions(device_asm(source))
     assert sum(len(lds_loads(b)) for b in kernels.values()) > 50
     bad = [(name[:80], x) for name, blocks in kernels.items() for x in early_m0(blocks)]
+    assert not bad, (len(bad), bad[:3])
+
+
+@pytest.mark.parametrize("source", SOURCES)
+def test_scalars_of_memory_accesses_are_settled(source):
+    kernels = functions(device_asm(source))
+    bad = [(name[:80], x) for name, blocks in kernels.items() for x in early_scalars(blocks)]
     assert not bad, (len(bad), bad[:3])
