@@ -355,6 +355,8 @@ template <int OFF>
 __device__ __forceinline__ void xrd(half8& d, uint32_t a) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(a), "n"(OFF));
 }
+// c becomes a value (and AGPRs) of its own
+__device__ __forceinline__ void xown(f32x4& c) { asm volatile("" : "+a"(c)); }
 // c += a b (16x16x32), c in AGPRs
 __device__ __forceinline__ void xmma(f32x4& c, const half8& a, const half8& b) {
   asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
@@ -589,6 +591,14 @@ gemm_f16_kernel(int64_t M, int64_t N, int64_t K, float alpha,
     };
     using Z0 = std::integral_constant<int, 0>;
     using Z1 = std::integral_constant<int, 1>;
+    // Every accumulator starts as a value of its own.  As copies of one zero
+    // the compiler may give an accumulator another register behind the first
+    // loop than inside it, and the move at that loop's exit reads it before
+    // its last MFMA has written it (asm MFMAs are outside the hazard checks).
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) xown(acc[i][j]);
     // prologue: slices 0 .. NS-1 in flight (those past K fill their stage
     // with zeros), slice 0 resident, its first k-step's fragments into set 0
     auto kv_of = [&](int kt) {
