@@ -1168,7 +1168,8 @@ hipError_t dispatch_tile(const GemmArgs& g, hipStream_t s) {
     }
   }
   const bool split_k = EPI == 0 && g.ws != nullptr && gemm_splitk_ws_bytes(g.M, g.N, g.K) <= g.ws_bytes;
-  const GemmPlan p = gemm_plan(TA, g.M, EPI == 1 ? g.F : g.N, g.K, EPI, EPI == 0 && g.beta != 0.f, split_k);
+  const GemmPlan p = gemm_plan(TA, g.M, EPI == 1 ? g.F : g.N, g.K, EPI, EPI == 0 && g.beta != 0.f, split_k,
+                               ((g.lda | g.ldb) & 63) != 0);
   GemmArgs tail = g;
   if (p.split_at > 0) {
     GemmArgs head = g;

@@ -73,8 +73,10 @@ struct GemmPlan {
   int splits;
 };
 // N in output columns (gate columns for epilogue 1); split_k: the caller's
-// workspace holds gemm_splitk_ws_bytes(M, N, K).
-GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k);
+// workspace holds gemm_splitk_ws_bytes(M, N, K); split_rows: lda or ldb is no
+// multiple of 64 elements (rows do not start on memory lines).
+GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k,
+                   bool split_rows = false);
 
 struct AttnShape {
   int B, S, Hq, Hkv, D;

@@ -81,36 +81,49 @@ constexpr int64_t kPlanCUs = 256;
 // {4096, 11008} NT take 96 / 257 us as 256x256 tiles, 57 / 154 as 256x128,
 // 42 / 110 as 128x128, 77 / 194 as 64x64; 4096 x 4096 x {4096, 11008} 109 / 285,
 // 123 / 321, 154 / 411, 297 / 745.
+// Leading dimensions that are no multiple of 64 elements (`split_rows`): the
+// 128 bytes that a slice reads of each row then lie in two memory lines.  The
+// larger tiles hide that behind their MFMAs; the 64x64 tile's slices take
+// 1.2 (TN 1.3) times as long, the 128x128 tile's 1.07.  Over 880 random
+// shapes with K from 64 to 16384, 626 of them with a split-K plan: without
+// these factors 70 ran as whole-K tiles more than 10% slower than split (128 x
+// 5160 x 10616 NT 88 us against 54), with them 19, the worst 1.26 times.
 struct TileCost {
-  double slice, slice_tn, load, fixed[3], r;
+  double slice, slice_tn, load, fixed[3], r, split_rows, split_rows_tn;
 };
 constexpr TileCost kTileCost[kNumGemmTiles] = {
-    {1.48, 1.42, 0.10, {4.0, 6.0, 18.0}, 6.0},
-    {0.87, 0.92, 0.03, {3.0, 4.5, 11.0}, 3.0},
-    {0.87, 0.92, 0.03, {3.0, 4.5, 13.0}, 3.0},
-    {0.50, 0.55, 0.10, {1.5, 2.0, 6.0}, 1.5},
-    {0.25, 0.26, 0.02, {1.5, 3.0, 5.5}, 0.5},
+    {1.48, 1.42, 0.10, {4.0, 6.0, 18.0}, 6.0, 1.0, 1.0},
+    {0.87, 0.92, 0.03, {3.0, 4.5, 11.0}, 3.0, 1.0, 1.0},
+    {0.87, 0.92, 0.03, {3.0, 4.5, 13.0}, 3.0, 1.0, 1.0},
+    {0.50, 0.55, 0.10, {1.5, 2.0, 6.0}, 1.5, 1.07, 1.0},
+    {0.25, 0.26, 0.02, {1.5, 3.0, 5.5}, 0.5, 1.2, 1.3},
 };
 constexpr double kLaunchUs = 4.0;             // a further launch in the stream
 constexpr double kPartialBytesPerUs = 9.0e6;  // split-K partials, written, then read
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// what one call's tiles have in common
+struct TileKind {
+  bool tn, split_rows;
+  int epi;
+};
+
 // us of `tiles` tiles of a kind, nk K-slices each
-double tiles_cost(int tile, bool tn, int epi, bool reads_r, int64_t tiles, int64_t nk) {
+double tiles_cost(int tile, const TileKind& k, bool reads_r, int64_t tiles, int64_t nk) {
   const TileCost& c = kTileCost[tile];
+  const double slice = (k.tn ? c.slice_tn : c.slice) * (!k.split_rows ? 1.0 : k.tn ? c.split_rows_tn : c.split_rows);
   auto round = [&](int64_t n) {
-    return (double)nk * ((tn ? c.slice_tn : c.slice) + c.load * (double)n / kPlanCUs) + c.fixed[epi] +
-           (reads_r ? c.r : 0.0);
+    return (double)nk * (slice + c.load * (double)n / kPlanCUs) + c.fixed[k.epi] + (reads_r ? c.r : 0.0);
   };
   const int64_t full = tiles / kPlanCUs, rem = tiles % kPlanCUs;
   return (double)full * round(kPlanCUs) + (rem ? round(rem) : 0.0);
 }
 
 // ... of an M x N region
-double region_cost(int tile, bool tn, int epi, bool reads_r, int64_t M, int64_t N, int64_t nk) {
-  const int64_t bn = epi == 1 ? kGemmTileDim[tile].n / 2 : kGemmTileDim[tile].n;
-  return tiles_cost(tile, tn, epi, reads_r, ceil_div(M, kGemmTileDim[tile].m) * ceil_div(N, bn), nk);
+double region_cost(int tile, const TileKind& k, bool reads_r, int64_t M, int64_t N, int64_t nk) {
+  const int64_t bn = k.epi == 1 ? kGemmTileDim[tile].n / 2 : kGemmTileDim[tile].n;
+  return tiles_cost(tile, k, reads_r, ceil_div(M, kGemmTileDim[tile].m) * ceil_div(N, bn), nk);
 }
 
 }  // namespace
@@ -124,8 +137,9 @@ double region_cost(int tile, bool tn, int epi, bool reads_r, int64_t M, int64_t 
 //     tiles with K split; it pays where few tiles face a long K.
 // Larger tiles cost less per FLOP (the 256x256 tile's slice: 1.56 us, four
 // 128x128 slices: 2.4 us), smaller ones fill the CUs and their last round.
-GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k) {
-  const bool tn = transA != 0;
+GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k,
+                   bool split_rows) {
+  const TileKind kind{transA != 0, split_rows, epi};
   const int64_t nk = ceil_div(K, 64);
   GemmPlan best{true, 0, kTile256, kTile256, 1};
   double best_us = 1e30;
@@ -136,7 +150,7 @@ GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool re
     }
   };
   for (int t = 0; t < kNumGemmTiles; ++t)
-    offer(GemmPlan{true, 0, t, t, 1}, region_cost(t, tn, epi, reads_r, M, N, nk));
+    offer(GemmPlan{true, 0, t, t, 1}, region_cost(t, kind, reads_r, M, N, nk));
   const int64_t un = epi == 1 ? 128 : 256;         // output columns per 256-wide tile
   const int64_t tm = ceil_div(M, 256), tc = ceil_div(N, un);
   for (int cols = 0; cols < 2; ++cols) {
@@ -146,11 +160,11 @@ GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool re
     if (rounds < 1 || across > kPlanCUs) continue;
     const int64_t n = rounds * kPlanCUs / across;  // tile columns (rows) in whole rounds
     if (n < 1 || n >= along) continue;
-    const double head = tiles_cost(kTile256, tn, epi, reads_r, n * across, nk);
+    const double head = tiles_cost(kTile256, kind, reads_r, n * across, nk);
     const int64_t at = n * (cols ? un : 256);
     for (int t = 0; t < kNumGemmTiles; ++t)
       offer(GemmPlan{cols == 1, at, kTile256, t, 1},
-            head + kLaunchUs + region_cost(t, tn, epi, reads_r, cols ? M : M - at, cols ? N - at : N, nk));
+            head + kLaunchUs + region_cost(t, kind, reads_r, cols ? M : M - at, cols ? N - at : N, nk));
   }
   SplitTail st;
   if (split_k && epi == 0 && gemm_splitk_tail(M, N, K, &st)) {
@@ -158,8 +172,8 @@ GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool re
     const int64_t rest = tm * tc - tail;
     const double sum = 2.0 * 4.0 * st.S * (double)st.Mt * (double)st.Nt / kPartialBytesPerUs;
     offer(GemmPlan{st.columns, st.split_at, kTile256, kTile256, st.S},
-          tiles_cost(kTile256, tn, 0, reads_r, rest, nk) + (rest ? kLaunchUs : 0.0) +
-              tiles_cost(kTile256, tn, 0, false, tail * st.S, ceil_div(nk, st.S)) + kLaunchUs + sum);
+          tiles_cost(kTile256, kind, reads_r, rest, nk) + (rest ? kLaunchUs : 0.0) +
+              tiles_cost(kTile256, kind, false, tail * st.S, ceil_div(nk, st.S)) + kLaunchUs + sum);
   }
   return best;
 }

@@ -1,8 +1,11 @@
+import collections
+import ctypes
 import functools
 import json
 import math
 import os
 import re
+import shutil
 import subprocess
 import sys
 import tempfile
@@ -35,6 +38,42 @@ def device_asm(source):
                         os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
         with open(out) as f:
             return f.read().split("\n")
+
+
+@functools.lru_cache(maxsize=None)
+def _plan_library():
+    """The host-side plans (plan_query.cpp, plan.cpp), compiled once per run; skips where g++ is missing."""
+    if shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include/hip"):
+        pytest.skip("needs g++ and the HIP headers")
+    with tempfile.TemporaryDirectory() as d:
+        out = os.path.join(d, "plan_query.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                        "-I/opt/rocm/include", f"-I{ROOT}/include", os.path.join(ROOT, "tests", "plan_query.cpp"),
+                        os.path.join(ROOT, "paper_2606_10415_amd", "csrc", "plan.cpp"), "-o", out], check=True)
+        return ctypes.CDLL(out)
+
+
+GemmPlan = collections.namedtuple("GemmPlan", "columns split_at head tail splits")
+
+
+def gemm_plan(transA, transB, M, N, K, epi=0, reads_r=False, ws=False):
+    """How a GEMM call with tight operands (leading dimensions rounded up to 8)
+    is launched: `head` tiles up to column (columns) or row split_at, `tail`
+    tiles behind it, the tail's K split `splits` ways.  N in output columns
+    (gate columns for epi 1)."""
+    out = (ctypes.c_int64 * 7)()
+    up8 = lambda n: -(-n // 8) * 8
+    lda, ldb = up8(M if transA else K), up8(K if transB else N)
+    _plan_library().query_gemm_plan(int(transA), *(ctypes.c_int64(n) for n in (M, N, K)), epi, int(reads_r), int(ws),
+                                    int((lda | ldb) & 63 != 0), out)
+    return GemmPlan(bool(out[0]), out[1], (out[2], out[3]), (out[4], out[5]), out[6])
+
+
+def attn_shares(B, S, Hq, Hkv, D, causal):
+    """(key tile width, shares per key tile) of the attention backward's dK/dV pass."""
+    n, tiles = (ctypes.c_int * 512)(), ctypes.c_int()
+    ktile = _plan_library().query_attn_shares(B, S, Hq, Hkv, D, int(causal), n, ctypes.byref(tiles))
+    return ktile, list(n[:tiles.value])
 
 
 def load_golden(name):

@@ -15,6 +15,7 @@ import numpy as np
 import pytest
 
 import oracle
+from conftest import gemm_plan
 from paper_2606_10415_amd.synth import uniform_int_f16
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -110,3 +111,14 @@ def test_plan_tiles_exact_integers(transA, transB, M, N, K, ws):
     ref = oracle.gemm(0, 0, 3.0, a[rows], b, -2.0, r[rows]).astype(np.float16)
     assert np.array_equal(got[rows].view(np.uint16), ref.view(np.uint16))
     assert (got[M] == 777.0).all()
+
+
+@pytest.mark.parametrize("transA,transB,M,N,K,splits", [
+    # rows that lie across memory lines: whole-K 64x64 tiles take 88, 51, 30
+    # and 61 us, split ones 54, 33, 24 and 44
+    (0, 1, 128, 5160, 10616, 8), (1, 0, 120, 3272, 6504, 8), (0, 0, 152, 952, 5712, 8), (0, 1, 312, 1072, 8344, 8),
+    # rows on memory lines: 20 us whole, 29 us split
+    (0, 1, 480, 976, 5760, 1),
+])
+def test_split_of_skinny_products(transA, transB, M, N, K, splits):
+    assert gemm_plan(transA, transB, M, N, K, ws=True).splits == splits
