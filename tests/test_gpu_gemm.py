@@ -16,7 +16,7 @@ import pytest
 
 import oracle
 from paper_2606_10415_amd.synth import normal_f16, uniform_int_f16, WORKLOADS
-from conftest import rel_f
+from conftest import gemm_plan, rel_f
 
 pytestmark = pytest.mark.gpu
 
@@ -56,7 +56,7 @@ LAYOUTS = list(itertools.product([0, 1], [0, 1]))
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (136, 200, 72), (264, 520, 1000), (4096, 4096, 512),
-                                   # a last wave of at most half the CUs runs as half-size tiles:
+                                   # a last wave of at most half the CUs runs as smaller tiles:
                                    # column split (8 x 34 tiles), row split (34 x 8), ragged edges
                                    (2048, 8704, 256), (8704, 2048, 256), (2040, 8696, 264),
                                    (8696, 2040, 264)])
@@ -78,7 +78,7 @@ def test_gemm_exact_integers_bitwise(env, transA, transB, M, N, K):
     (4096, 3072, 320),    # 5 slices (odd), all whole
     (4000, 3112, 4104),   # 65 slices, the last 8 wide; M and N tails
     (3848, 3328, 200),    # 4 slices, the last 8 wide; M and N tails
-    (4096, 3072, 8),      # a single 8-wide slice
+    (4096, 3072, 8),      # a single 8-wide slice (128x128 tiles; 256x256 in test_gemm_plan.py)
 ])
 def test_gemm_four_wave_slices_exact_integers_bitwise(env, transA, transB, M, N, K):
     print(f"gemm 4-wave slices trans=({transA},{transB}) M={M} N={N} K={K}", flush=True)
@@ -199,8 +199,8 @@ def test_gemm_full_size_sampled(env, name, transA, transB, M, N, K):
     assert rel_f(got, ref) <= 5e-3
 
 
-# ---- lt_gemm_f16_ws: the last, at most half full, wave of 256x256 tiles with its
-# K split over several workgroups (FP32 partials in the caller's workspace) ----
+# ---- lt_gemm_f16_ws: shapes whose workspace has room for a split K.  Which of
+# them run split is the launch plan's choice: test_gemm_ws_split_plans pins it. ----
 
 def _run_ws(env, transA, transB, M, N, K, alpha, a, b, beta, r, bias=None, inplace=False):
     torch, lt = env
@@ -210,7 +210,7 @@ def _run_ws(env, transA, transB, M, N, K, alpha, a, b, beta, r, bias=None, inpla
     C = R if inplace else torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
     Bias = None if bias is None else torch.from_numpy(bias).cuda()
     need = lt.lt_gemm_f16_workspace_size(transA, transB, M, N, K)
-    assert need > 0, "shape must take the split-K tail"
+    assert need > 0, "the workspace has room for a split"
     ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")   # contents unused
     lt.lt_gemm_f16_ws(transA, transB, M, N, K, alpha, A, A.shape[1], B, B.shape[1], beta, R, N,
                       Bias, C, N, ws, need)
@@ -226,15 +226,15 @@ def _tail_rows(M, n=40, seed=3):
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 @pytest.mark.parametrize("M,N,K,bias,inplace", [
-    (4096, 5120, 2048, False, False),   # column tail (columns 4096..), S = 4
-    (5120, 4096, 1024, True, False),    # row tail (rows 4096..), S = 2, bias
-    (4088, 5112, 1000, False, True),    # ragged M/N/K, ragged last split, C = R in place
+    (4096, 5120, 2048, False, False),   # whole rounds, then columns 4096.. as 128x128 tiles
+    (5120, 4096, 1024, True, False),    # ... rows 4096.., bias
+    (4088, 5112, 1000, False, True),    # ... ragged M/N/K, C = R in place
     (1024, 1536, 4096, True, False),    # 24 tiles, split whole (S = 8), bias
     (1000, 1544, 4136, False, True),    # 28 tiles, split whole (S = 8), ragged, in place
-    (2048, 3000, 4104, False, False),   # 96 tiles, split whole (S = 2), ragged N and K
+    (2048, 3000, 4104, False, False),   # one launch of 256x128 tiles, ragged N and K
 ])
 def test_gemm_ws_split_tail_exact_integers(env, transA, transB, M, N, K, bias, inplace):
-    """Integer-valued inputs keep every FP32 partial and sum exact, so the split
+    """Integer-valued inputs keep every FP32 partial and sum exact, so the
     result equals RNE(oracle) bit for bit on sampled rows of head and tail."""
     print(f"gemm ws split tail trans=({transA},{transB}) M={M} N={N} K={K}", flush=True)
     a = uniform_int_f16(21, (M, K), -2, 2)
@@ -250,9 +250,41 @@ def test_gemm_ws_split_tail_exact_integers(env, transA, transB, M, N, K, bias, i
 
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("M,N,K,bias,inplace,columns,split_at,splits", [
+    # whole rounds of 256x256 tiles, then a tail with its K split: the last
+    # share has 2 of 9 slices (K = 4104), or all of its own (K = 3080)
+    (3848, 4360, 4104, True, False, True, 4096, 8),     # columns 4096..
+    (4360, 3848, 4104, False, True, False, 4096, 8),    # rows 4096.., in place
+    (3848, 4360, 3080, True, True, True, 4096, 6),
+    (4360, 3848, 3080, True, False, False, 4096, 6),
+    # split whole, ragged edges
+    (2040, 3072, 8200, True, True, True, 0, 2),
+    (784, 3848, 8200, False, False, True, 0, 4),
+    (264, 264, 6152, True, False, True, 0, 8),
+])
+def test_gemm_ws_split_plans(env, transA, transB, M, N, K, bias, inplace, columns, split_at, splits):
+    """Calls that do run split: the plan is asserted, the result exact as above."""
+    print(f"gemm ws split plan trans=({transA},{transB}) M={M} N={N} K={K}", flush=True)
+    p = gemm_plan(transA, transB, M, N, K, reads_r=True, ws=True)
+    assert (p.columns, p.split_at, p.splits) == (columns, split_at, splits)
+    a = uniform_int_f16(25, (M, K), -2, 2)
+    b = uniform_int_f16(26, (K, N), -2, 2)
+    r = uniform_int_f16(27, (M, N), -8, 8)
+    bv = uniform_int_f16(28, (N,), -4, 4) if bias else None
+    got = _run_ws(env, transA, transB, M, N, K, 3.0, a, b, -2.0, r, bv, inplace)
+    rows = _tail_rows(M)
+    ref = oracle.gemm(0, 0, 3.0, a[rows], b, -2.0, r[rows])
+    if bias:
+        ref = ref + bv.astype(np.float64)
+    assert np.array_equal(got[rows].view(np.uint16), ref.astype(np.float16).view(np.uint16))
+
+
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
 def test_gemm_ws_split_tail_normal_parity(env, transA, transB):
     M, N, K = 4096, 5120, 5120
     print(f"gemm ws split tail normal trans=({transA},{transB})", flush=True)
+    # columns 4096..: K split for transA, 128x128 tiles otherwise
+    assert gemm_plan(transA, transB, M, N, K, reads_r=True, ws=True)[:2] == (True, 4096)
     a = normal_f16(31, (M, K))
     b = normal_f16(32, (K, N), 0.02)
     r = normal_f16(33, (M, N))
@@ -260,4 +292,4 @@ def test_gemm_ws_split_tail_normal_parity(env, transA, transB):
     rows = _tail_rows(M, 24)
     ref = oracle.gemm(0, 0, 1.0, a[rows], b, 1.0, r[rows])
     assert rel_f(got[rows], ref) <= 5e-3
-    assert rel_f(got[rows][:, 4096:], ref[:, 4096:]) <= 5e-3      # the split columns alone
+    assert rel_f(got[rows][:, 4096:], ref[:, 4096:]) <= 5e-3      # the tail's columns alone

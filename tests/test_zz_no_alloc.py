@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import oracle
+from conftest import gemm_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -41,7 +42,7 @@ def _both(env, tA, tB, M, N, K, a, b, beta=0.0, r=None, bias=None):
     R = torch.from_numpy(r).cuda() if r is not None else None
     bi = torch.from_numpy(bias).cuda() if bias is not None else None
     need = lt.lt_gemm_f16_workspace_size(tA, tB, M, N, K)
-    assert 0 < need <= lt.LT_GEMM_NOALLOC_SCRATCH_BYTES, need      # the split path is exercised
+    assert 0 < need <= lt.LT_GEMM_NOALLOC_SCRATCH_BYTES, need      # there is room for a split
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     C_ws = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
     C_na = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
@@ -52,9 +53,8 @@ def _both(env, tA, tB, M, N, K, a, b, beta=0.0, r=None, bias=None):
     return C_ws.cpu().numpy(), C_na.cpu().numpy()
 
 
-# (transA, transB, M, N, K): whole-launch splits (under one wave of 256x256
-# tiles, 8 shares) and a last-wave split (the LLaMA-2-7B gate/up forward
-# shape), each followed by a smaller call.
+# (transA, transB, M, N, K), each followed by a smaller call; of these the
+# launch plan splits the last only (S = 4).
 PAIRS = [
     ((1, 0, 1024, 1024, 8192), (1, 0, 512, 512, 4096)),
     ((0, 1, 4096, 22016, 4096), (0, 0, 1024, 4096, 22016)),
@@ -77,7 +77,7 @@ def test_noalloc_matches_workspace_entry_point(env, first, second):
 
 def test_noalloc_integer_exact_with_residual_and_bias(env):
     """Integer operands (|sums| < 2^24): every output equals RNE(oracle) bit for bit,
-    with beta * R and the bias added in the split's reduction; then a smaller call."""
+    with beta * R and the bias; then a smaller call (both run as 64x64 tiles)."""
     rng = np.random.default_rng(11)
     for tA, tB, M, N, K in ((1, 0, 1024, 1024, 8192), (0, 0, 512, 512, 4096)):
         print(f"noalloc integer: transA={tA} transB={tB} M={M} N={N} K={K}", flush=True)
@@ -88,3 +88,25 @@ def test_noalloc_integer_exact_with_residual_and_bias(env):
         ref = oracle.gemm(tA, tB, 1.0, a, b, 1.0, r.astype(np.float64)) + bias.astype(np.float64)
         assert np.array_equal(c_na.view(np.uint16), ref.astype(np.float16).view(np.uint16))
         assert np.array_equal(c_ws.view(np.uint16), c_na.view(np.uint16))
+
+
+def test_noalloc_splits_share_the_array(env):
+    """Calls that the launch plan splits (asserted), one after the other on the one static array, the partials of
+    each smaller than those before: a column tail, a row tail, whole launches.  Integer operands, so beta * R and
+    the bias, added in the split's reduction, leave every output equal to RNE(oracle) bit for bit."""
+    rng = np.random.default_rng(13)
+    for tA, tB, M, N, K, where in ((0, 1, 3848, 4360, 4104, (True, 4096, 8)), (1, 0, 4360, 3848, 3080, (False, 4096, 6)),
+                                   (1, 0, 1000, 1544, 8264, (True, 0, 8)), (0, 0, 264, 520, 8200, (True, 0, 8)),
+                                   (1, 1, 264, 264, 6152, (True, 0, 8))):
+        print(f"noalloc split: transA={tA} transB={tB} M={M} N={N} K={K}", flush=True)
+        p = gemm_plan(tA, tB, M, N, K, reads_r=True, ws=True)
+        assert (p.columns, p.split_at, p.splits) == where
+        a, b = _operands(rng, tA, tB, M, N, K, integer=True)
+        r = rng.integers(-4, 5, (M, N)).astype(np.float16)
+        bias = rng.integers(-3, 4, (N,)).astype(np.float16)
+        c_ws, c_na = _both(env, tA, tB, M, N, K, a, b, beta=1.0, r=r, bias=bias)
+        assert np.array_equal(c_ws.view(np.uint16), c_na.view(np.uint16))
+        rows = np.unique(np.concatenate([rng.choice(M, 40, replace=False), [0, M - 1]]))
+        ref = oracle.gemm(tA, tB, 1.0, a[:, rows] if tA else a[rows], b, 1.0, r[rows].astype(np.float64))
+        ref = ref + bias.astype(np.float64)
+        assert np.array_equal(c_na[rows].view(np.uint16), ref.astype(np.float16).view(np.uint16))
