@@ -1,10 +1,12 @@
 """Launch plans of the GEMM: which tiles a call runs as (host code), and the tiles on the GPU.
 
-CPU: the plan's regions cover the output once, on tile boundaries, for random
-sizes, epilogues and layouts; split-K plans only where the workspace rule has one.
-GPU: one shape per kind of plan and layout (ragged rows, columns and K among
-them) with integer operands, whose FP32 sums are exact, so the result equals the
-float64 product bit for bit.
+CPU: a plan's cut lies on a tile edge inside the output, for random sizes,
+epilogues and layouts; split-K plans only where the workspace rule has one.
+GPU: every tile in every layout and epilogue, by itself and behind whole rounds
+of 256x256 tiles, at ragged sizes.  The plan of each is asserted, so that another
+cost model cannot drop one silently.  Integer operands, whose FP32 sums are
+exact, so the plain results equal the float64 product bit for bit; the SwiGLU
+epilogues meet the bars of their parity test.
 """
 
 import os
@@ -15,6 +17,7 @@ import numpy as np
 import pytest
 
 import oracle
+import test_gpu_swiglu_layer as fused
 from conftest import gemm_plan
 from paper_2606_10415_amd.synth import uniform_int_f16
 
@@ -79,12 +82,16 @@ def test_plans_cover_the_output(tmp_path):
     (65, 72, 64, False),        # 64x64 tiles, one slice in the eight-stage ring
     (200, 328, 584, False),     # 64x64, more slices than stages, last slice 8 wide
     (1000, 4096, 328, False),   # 128x128
-    (1237, 5120, 456, False),   # two-launch and 256x128 plans, ragged rows
-    (2048, 4096, 1224, False),  # 256x128 or 128x256, one round
-    (1237, 7168, 200, True),    # workspace given, not taken
-    (1104, 4120, 1237, False),  # K odd: whole k-rows for weight gradients, fix-up elsewhere
+    (1237, 5120, 456, False),   # 256x128, one launch, ragged rows
+    (2048, 4096, 1224, False),  # 256x128, one round
+    (1237, 7168, 200, True),    # 256x256, workspace given, not taken
+    (1104, 4120, 1237, False),  # K odd: 128x256 with whole k-rows for weight gradients, fix-up elsewhere
 ])
 def test_plan_tiles_exact_integers(transA, transB, M, N, K, ws):
+    run_exact(transA, transB, M, N, K, ws)
+
+
+def run_exact(transA, transB, M, N, K, ws):
     import torch
     from paper_2606_10415_amd import lt
 
@@ -98,19 +105,72 @@ def test_plan_tiles_exact_integers(transA, transB, M, N, K, ws):
         out[:, :st.shape[1]] = st
         return torch.from_numpy(out).cuda()
 
-    A, B, R = stored(a, transA), stored(b, transB), torch.from_numpy(r).cuda()
-    C = torch.full((M + 1, N), 777.0, dtype=torch.float16, device="cuda")           # a guard row
+    A, B, R = stored(a, transA), stored(b, transB), stored(r, False)
+    ldc = -(-N // 8) * 8
+    C = torch.full((M + 1, ldc), 777.0, dtype=torch.float16, device="cuda")         # a guard row, guard columns
     if ws:
         need = max(lt.lt_gemm_f16_workspace_size(transA, transB, M, N, K), 16)
         w = torch.empty(need, dtype=torch.uint8, device="cuda")
-        lt.lt_gemm_f16_ws(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, N, None, C, N, w, need)
+        lt.lt_gemm_f16_ws(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, ldc, None, C, ldc, w,
+                          need)
     else:
-        lt.lt_gemm_f16_res(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, N, C, N)
+        lt.lt_gemm_f16_res(transA, transB, M, N, K, 3.0, A, A.shape[1], B, B.shape[1], -2.0, R, ldc, C, ldc)
     got = C.cpu().numpy()
     rows = np.unique(np.concatenate([np.random.default_rng(0).choice(M, min(M, 96), replace=False), [0, M - 1]]))
     ref = oracle.gemm(0, 0, 3.0, a[rows], b, -2.0, r[rows]).astype(np.float16)
-    assert np.array_equal(got[rows].view(np.uint16), ref.view(np.uint16))
-    assert (got[M] == 777.0).all()
+    assert np.array_equal(np.ascontiguousarray(got[rows, :N]).view(np.uint16), ref.view(np.uint16))
+    assert (got[M] == 777.0).all() and (got[:, N:] == 777.0).all()
+
+
+ONE, COLUMNS, ROWS = "one launch", "columns", "rows"
+
+
+def planned(p):
+    return (ONE if p.split_at == 0 else COLUMNS if p.columns else ROWS), p.tail
+
+
+# more slices than the tile has LDS stages, a last slice of 8 columns; ragged
+# rows, columns and packed columns
+@pytest.mark.gpu
+@pytest.mark.parametrize("transA,transB", [(0, 1), (0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,plan", [
+    (61, 200, 1000, (ONE, (64, 64))),
+    (3003, 328, 328, (ONE, (128, 128))),
+    (777, 4675, 328, (ONE, (128, 256))),
+    (901, 4131, 328, (ONE, (256, 128))),
+    (2600, 3083, 200, (ONE, (256, 256))),
+    (4000, 4088, 8, (ONE, (256, 256))),            # a single 8-wide slice
+    (3848, 5107, 328, (COLUMNS, (128, 128))),
+    (5107, 3848, 328, (ROWS, (128, 128))),
+    (2040, 8691, 264, (COLUMNS, (64, 64))),
+    (8691, 2040, 264, (ROWS, (64, 64))),
+])
+def test_every_tile_and_layout(transA, transB, M, N, K, plan):
+    assert planned(gemm_plan(transA, transB, M, N, K, reads_r=True)) == plan
+    run_exact(transA, transB, M, N, K, False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,H,F,gate_up,swiglu_bwd", [
+    (56, 1000, 200, (ONE, (64, 64)), (ONE, (64, 64))),
+    (200, 328, 4120, (ONE, (128, 128)), (ONE, (128, 128))),
+    (1544, 328, 4680, (ONE, (128, 256)), (ONE, (128, 256))),
+    (3000, 328, 712, (ONE, (256, 128)), (ONE, (128, 128))),
+    (2600, 200, 1544, (ONE, (256, 256)), (ONE, (256, 128))),
+    (4088, 328, 2600, (COLUMNS, (256, 128)), (ONE, (256, 256))),
+    (3000, 328, 4088, (ROWS, (256, 128)), (ONE, (256, 256))),
+    (3848, 328, 5112, (COLUMNS, (128, 256)), (COLUMNS, (128, 128))),
+    (5112, 328, 3848, (COLUMNS, (256, 128)), (ROWS, (128, 128))),
+    (2600, 328, 3848, (ROWS, (128, 256)), (ONE, (256, 256))),
+    (2600, 1000, 3080, (ROWS, (64, 64)), (ONE, (256, 256))),
+])
+def test_every_tile_of_the_swiglu_epilogues(T, H, F, gate_up, swiglu_bwd):
+    import torch
+    from paper_2606_10415_amd import lt
+
+    assert planned(gemm_plan(0, 1, T, F, H, epi=1)) == gate_up
+    assert planned(gemm_plan(0, 0, T, F, H, epi=2)) == swiglu_bwd
+    fused.test_fused_gemm_swiglu_parity((torch, lt), T, H, F)
 
 
 @pytest.mark.parametrize("transA,transB,M,N,K,splits", [

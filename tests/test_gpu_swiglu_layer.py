@@ -62,7 +62,7 @@ def test_swiglu_extreme_inputs(env):
 @pytest.mark.parametrize("T,H,F", [(272, 256, 344), (64, 128, 688), (8, 64, 8), (1000, 512, 1000),
                                    (4096, 4096, 11008), (2048, 5120, 13824),
                                    (2040, 512, 5000),
-                                   # half-size tail tiles: column split of both epilogues,
+                                   # smaller tail tiles: column split of both epilogues,
                                    # row split of both, and ragged versions
                                    (2048, 256, 8704), (8704, 256, 2048), (2040, 256, 8696),
                                    (8696, 256, 2040)])
