@@ -3,8 +3,8 @@
 CPU: for random shapes the shares cover every tile, no workgroup is empty, and
 the partial rows fit the workspace that lt_attn_bwd_workspace_size asks for.
 GPU: shapes whose tiles get unequal shares (several, one written directly, a
-ragged last tile, one tile only) against a float64 reference, recomputed and
-saved P; bars as for the other backward tests (FP16 results of FP32 sums over
+ragged last tile, one tile only; 256- and 128-key tiles) against a float64
+reference, recomputed and saved P; the shares of each are asserted; bars as for the other backward tests (FP16 results of FP32 sums over
 FP16 P and dS: 1e-2 of the gradient's norm).
 """
 
@@ -15,7 +15,7 @@ import subprocess
 
 import pytest
 
-from conftest import rel_f
+from conftest import attn_shares, rel_f
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = "/opt/rocm"
@@ -70,19 +70,43 @@ def test_shares_cover_the_tiles_within_the_workspace(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr[-2000:]
 
 
+# key tile width and shares per key tile of each GPU case
+PLANNED = {
+    (1, 1300, 10, 2, 128, True): (256, [7, 6, 5, 3, 2, 1]),
+    (1, 700, 4, 4, 64, True): (128, [1] * 6),
+    (2, 200, 8, 1, 64, True): (256, [16]),
+    (1, 1024, 8, 2, 128, False): (256, [16] * 4),
+    (4, 333, 16, 16, 64, False): (128, [1] * 3),
+    (1, 1500, 4, 4, 128, True): (128, [3, 3, 3, 2, 2, 2, 2, 2, 1, 1, 1, 1]),
+    (1, 1500, 4, 4, 64, True): (128, [3, 3, 3, 2, 2, 2, 2, 2, 1, 1, 1, 1]),
+    (6, 884, 1, 1, 128, True): (128, [3, 2, 2, 2, 1, 1, 1]),
+    (3, 2304, 1, 1, 64, False): (128, [2] * 18),
+}
+
+
+def test_planned_shares():
+    for case, plan in PLANNED.items():
+        assert attn_shares(*case) == plan, case
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("saved", [False, True], ids=["recomputed", "saved-P"])
 @pytest.mark.parametrize("B,S,Hq,Hkv,D,causal", [
     (1, 1300, 10, 2, 128, True),     # 256-key tiles, ragged last tile, many shares for the first
-    (1, 700, 4, 4, 64, True),        # 128-key tiles (query halves per wave pair)
+    (1, 700, 4, 4, 64, True),        # 128-key tiles, not split
     (2, 200, 8, 1, 64, True),        # one tile only
     (1, 1024, 8, 2, 128, False),     # equal work, no mask
     (4, 333, 16, 16, 64, False),     # one workgroup per tile although the workspace has room
+    (1, 1500, 4, 4, 128, True),      # 128-key tiles (query halves per wave pair), shares, ragged last tile
+    (1, 1500, 4, 4, 64, True),
+    (6, 884, 1, 1, 128, True),       # ... several batches
+    (3, 2304, 1, 1, 64, False),      # ... no mask
 ])
 def test_uneven_shares_against_float64(B, S, Hq, Hkv, D, causal, saved):
     import torch
     from paper_2606_10415_amd import lt
 
+    assert attn_shares(B, S, Hq, Hkv, D, causal) == PLANNED[B, S, Hq, Hkv, D, causal]
     print(f"shares B={B} S={S} Hq={Hq} Hkv={Hkv} D={D} causal={causal} saved={saved}", flush=True)
     T, row, hd, scale, ca = B * S, (Hq + 2 * Hkv) * D, Hq * D, 1 / math.sqrt(D), int(causal)
     g = torch.Generator().manual_seed(5)

@@ -218,10 +218,10 @@ CASES = [
     # 128-key workgroups whose wave pairs split the query halves; under 512
     # workgroups of the chosen tile, workspace shares.  Every case above
     # takes the split forward and dQ.
-    (2, 300, 256, 32, 64, True),   # fwd 128-query, dQ 256-query, dK/dV 256-key 4 shares; GQA 8:1
+    (2, 300, 256, 32, 64, True),   # fwd 128-query, dQ 256-query, dK/dV 256-key, shares; GQA 8:1
     (1, 264, 256, 256, 64, False), # fwd 128-query, dQ 256-query, dK/dV 256-key, non-causal
     (1, 1000, 64, 64, 64, True),   # dK/dV 128-key, no shares (512 workgroups), ragged
-    (2, 200, 4, 4, 128, True),     # MHA, batch 2, ragged: every split form with shares
+    (2, 200, 4, 4, 128, True),     # MHA, batch 2, ragged: room for shares, not split
     (2, 160, 2, 2, 128, False),    # the same, non-causal
 ]
 
