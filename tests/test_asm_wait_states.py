@@ -1,16 +1,18 @@
-"""Wait states around the asm direct loads, on the kernels' gfx950 assembly.
+"""Wait states around the asm statements, on the kernels' gfx950 assembly.
 
 The compiler inserts the wait states that the hardware does not interlock, but
 only between instructions of its own: what an asm statement holds, and the
 instructions just before it, are outside its checks.  The direct loads into
-LDS are such statements:
+LDS and the MFMAs of the GEMM's 4-wave loop are such statements:
 
   * a load into LDS reads m0, and needs one wait state after a scalar
     instruction has written it;
   * a buffer or global access needs five wait states after a vector
     instruction (v_readfirstlane, a compare, a spill's v_readlane) has written
     a scalar register that it reads, here a word of the buffer descriptor.  A
-    load with an old range would drop rows, or read past the matrix.
+    load with an old range would drop rows, or read past the matrix;
+  * an MFMA needs two wait states after a vector instruction has written one of
+    its operands (the compiler keeps them around MFMAs of its own).
 
 An instruction counts as one wait state, `s_nop n` as n + 1; distances are
 taken over every control-flow path.
@@ -133,6 +135,30 @@ def early_scalars(blocks):
     return bad
 
 
+def vectors(token):
+    m = re.match(r"([va])\[(\d+):(\d+)\]$", token.strip())
+    if m:
+        return {m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
+    return {token.strip()} if re.match(r"[va]\d+$", token.strip()) else set()
+
+
+def early_operands(blocks):
+    """MFMAs less than two wait states behind a vector write (not an MFMA's) of an operand."""
+    pred, bad = predecessors(blocks), []
+
+    def written(t):
+        op, _, rest = t.partition(" ")
+        return vectors(rest.split(",")[0]) if op.startswith("v_") and not op.startswith("v_mfma") else set()
+
+    for b, ins in blocks.items():
+        for i, t in enumerate(ins):
+            if t.startswith("v_mfma"):
+                reads = set().union(*(vectors(x) for x in t.partition(" ")[2].split(",")[1:]))
+                if waits_since(blocks, pred, b, i, 2, lambda x: written(x) & reads) is not None:
+                    bad.append((b, ins[max(0, i - 3):i + 1]))
+    return bad
+
+
 LOAD = "buffer_load_dwordx4 v1, s[4:7], 0 offen lds"
 
 
@@ -164,4 +190,18 @@ def test_m0_is_settled_before_a_load_into_lds(source):
 def test_scalars_of_memory_accesses_are_settled(source):
     kernels = functions(device_asm(source))
     bad = [(name[:80], x) for name, blocks in kernels.items() for x in early_scalars(blocks)]
+    assert not bad, (len(bad), bad[:3])
+
+
+def test_checker_finds_an_early_operand():
+    mfma = "v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], a[0:3]"
+    assert early_operands({"entry": ["v_mov_b32_e32 v9, v2", "s_waitcnt lgkmcnt(0)", mfma]})
+    assert early_operands({"entry": ["v_accvgpr_write_b32 a3, 0"], ".LBB0_1": [mfma]})
+    assert not early_operands({"entry": ["v_mov_b32_e32 v9, v2", "s_nop 1", mfma, mfma]})
+
+
+@pytest.mark.parametrize("source", SOURCES)
+def test_operands_of_mfmas_are_settled(source):
+    kernels = functions(device_asm(source))
+    bad = [(name[:80], x) for name, blocks in kernels.items() for x in early_operands(blocks)]
     assert not bad, (len(bad), bad[:3])

@@ -18,30 +18,18 @@ windows: the kernels would then read registers whose values have not landed.
 """
 
 import collections
-import os
 import re
-import shutil
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2606_10415_amd", "csrc")
-HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+from conftest import device_asm
+
 KERNEL = "gemm_f16_kernelILi256ELi256ELi2ELi2E"   # the 4-wave instantiations
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    if not os.path.exists(HIPCC):
-        pytest.skip("hipcc not available")
-    out = str(tmp_path_factory.mktemp("asm") / "gemm_f16.s")
-    subprocess.run([HIPCC, "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "--cuda-device-only", "-S",
-                    "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    "-Wno-unused-command-line-argument", "-x", "hip", os.path.join(CSRC, "gemm_f16.hip"),
-                    "-o", out], check=True, capture_output=True)
-    lines = open(out).read().split("\n")
+def kernels():
+    lines = device_asm("gemm_f16.hip")
     found = {}
     for i, line in enumerate(lines):
         if line.startswith("_Z") and KERNEL in line and line.split()[0].endswith(":"):

@@ -7,13 +7,9 @@ address sum) and the one that reads it.  The carry of an operand address is
 then lost where the sum crosses 4 GiB, or a loop's exit is missed.
 """
 
-import os
 import re
-import subprocess
 
-import pytest
-
-import test_gemm_asm_order as order
+from conftest import device_asm
 
 READERS = ("s_cbranch_scc0", "s_cbranch_scc1", "s_cselect_b32", "s_cselect_b64", "s_addc_u32", "s_subb_u32",
            "s_cmov_b32", "s_cmov_b64")
@@ -41,16 +37,8 @@ def test_checker_finds_a_lost_carry():
     assert not lost_conditions(["s_add_u32 m0, s9, 1024", "s_add_u32 s0, s0, s4", "s_addc_u32 s1, s1, 0"])
 
 
-def test_no_scalar_condition_is_lost_across_a_direct_load(tmp_path):
-    if not os.path.exists(order.HIPCC):
-        pytest.skip("hipcc not available")
-    out = str(tmp_path / "gemm_f16.s")
-    subprocess.run([order.HIPCC, "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "--cuda-device-only", "-S",
-                    "-I", os.path.join(order.ROOT, "include"), "-I", order.CSRC,
-                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    "-Wno-unused-command-line-argument", "-x", "hip", os.path.join(order.CSRC, "gemm_f16.hip"),
-                    "-o", out], check=True, capture_output=True)
-    lines = open(out).read().split("\n")
+def test_no_scalar_condition_is_lost_across_a_direct_load():
+    lines = device_asm("gemm_f16.hip")
     assert any("s_add_u32 m0" in x for x in lines)
     bad = lost_conditions(lines)
     assert not bad, bad[:5]

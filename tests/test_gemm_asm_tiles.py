@@ -7,29 +7,19 @@ smaller tiles hold 3 to 8 LDS stages and compute their fragment addresses
 inside the loop, so address arithmetic must keep out of these windows too.
 """
 
-import os
 import re
-import shutil
-import subprocess
 
 import pytest
 
 import test_gemm_asm_order as order
+from conftest import device_asm
 
 TILES = [(256, 256, 2), (256, 128, 3), (128, 256, 3), (128, 128, 4), (64, 64, 8)]
 
 
 @pytest.fixture(scope="module")
-def all_kernels(tmp_path_factory):
-    if not os.path.exists(order.HIPCC):
-        pytest.skip("hipcc not available")
-    out = str(tmp_path_factory.mktemp("asm") / "gemm_f16.s")
-    subprocess.run([order.HIPCC, "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "--cuda-device-only", "-S",
-                    "-I", os.path.join(order.ROOT, "include"), "-I", order.CSRC,
-                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                    "-Wno-unused-command-line-argument", "-x", "hip", os.path.join(order.CSRC, "gemm_f16.hip"),
-                    "-o", out], check=True, capture_output=True)
-    lines = open(out).read().split("\n")
+def all_kernels():
+    lines = device_asm("gemm_f16.hip")
     found = {}
     for i, line in enumerate(lines):
         if line.startswith("_Z") and "gemm_f16_kernelI" in line and line.split()[0].endswith(":"):
