@@ -129,7 +129,9 @@ static lt_status gemm_common(int transA, int transB, int64_t M, int64_t N, int64
     if (ws_bytes < need) return fail(LT_ERR_WORKSPACE, "workspace needs %zu bytes", need);
     if (!aligned16(workspace)) return fail(LT_ERR_UNSUPPORTED, "workspace must be 16-byte aligned");
   }
-  lt::GemmArgs g{transA, transB, M, N, K, alpha, beta, A, lda, B, ldb,
+  // (K = 0: the leading dimensions are unchecked, and the kernels' buffer
+  // ranges are formed from them)
+  lt::GemmArgs g{transA, transB, M, N, K, alpha, beta, A, K > 0 ? lda : 0, B, K > 0 ? ldb : 0,
                  beta != 0.f ? R : C, beta != 0.f ? ldr : ldc, C, ldc};
   g.bias = bias;
   g.ws = static_cast<float*>(workspace);

@@ -48,6 +48,10 @@ static void ws_inside(const void* p, size_t bytes, const char* what) {
 namespace lt {
 hipError_t gemm_f16_launch(const GemmArgs& g, hipStream_t) {
   ++g_launches;
+  // the kernels form buffer ranges from the leading dimensions, also of an
+  // empty reduction, whose operands the caller need not describe
+  CHECK(g.K > 0 ? g.lda > 0 && g.ldb > 0 : g.lda == 0 && g.ldb == 0, "gemm ranges lda %lld ldb %lld K %lld",
+        (long long)g.lda, (long long)g.ldb, (long long)g.K);
   if (g.ws) {
     const size_t need = gemm_splitk_ws_bytes(g.M, g.N, g.K);
     if (need <= g.ws_bytes) ws_inside(g.ws, need, "gemm split-K partials");
@@ -167,6 +171,8 @@ static void documented_cases() {
          LT_ERR_UNSUPPORTED, "gemm lda >= 2^22");
   expect(lt_gemm_f16(0, 1, 0, 64, 64, 1.f, nullptr, 0, nullptr, 0, 0.f, nullptr, 0, nullptr), LT_OK,
          "gemm M = 0 is a no-op");
+  expect(lt_gemm_f16(0, 1, 64, 64, 0, 1.f, nullptr, -8, nullptr, -8, 1.f, H, 64, nullptr), LT_ERR_HIP,
+         "gemm K = 0 reaches the launcher");
   expect(lt_gemm_f16_res(0, 1, 64, 64, 64, 1.f, H, 64, H, 64, 1.f, nullptr, 64, H, 64, nullptr),
          LT_ERR_INVALID_ARG, "gemm beta without R");
   int before = g_launches;

@@ -154,6 +154,11 @@ def test_gemm_beta_zero_ignores_nan_and_k_zero(env):
     torch.cuda.synchronize()
     ref = (0.5 * c2.astype(np.float64)).astype(np.float16)
     assert np.array_equal(C.cpu().numpy().view(np.uint16), ref.view(np.uint16))
+    # whatever the operands of the empty reduction are said to be
+    for transA, transB in LAYOUTS:
+        C = torch.from_numpy(c2).cuda()
+        lt.lt_gemm_f16(transA, transB, 64, 48, 0, 1.0, None, -8, None, -8, 0.5, C, 48)
+        assert np.array_equal(C.cpu().numpy().view(np.uint16), ref.view(np.uint16))
 
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
