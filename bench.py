@@ -33,9 +33,8 @@ PEAK_HBM_GBS = 8000.0
 
 # HBM traffic of the GEMM kernel at llama2-7b: mean bytes per GEMM call over the
 # 12 GEMM calls of one layer step (the paper's layer, SwiGLU in the gate/up and
-# down-dgrad epilogues; the gate/up forward runs as a 256x256 dispatch plus a
-# half-tile tail dispatch, its weight gradient as a 256x256 dispatch, split-K
-# partials of its last wave and their reduction, all counted as their call),
+# down-dgrad epilogues; calls that run as a dispatch of 256x256 tiles plus one
+# of smaller tail tiles count both as one call),
 # from two rocprofv3 --pmc runs of this script
 # (FETCH_SIZE, then WRITE_SIZE, with --copy-calibration-mib 1024) each scaled by
 # what the same counter reads for the calibration copy of known size.  The

@@ -143,12 +143,15 @@ lt_status lt_gemm_f16_bias(int transA, int transB, int64_t M, int64_t N,
  *
  *   Same conventions and errors as lt_gemm_f16_res; bias may be NULL (no
  *   bias), else [N] FP16, 16-byte aligned.  The workspace lets the kernel
- *   split the reduction (K) of output tiles over several workgroups: the
- *   tiles of a last, at most half full, wave of 256x256 tiles, or all tiles
- *   of a launch of less than about one wave when the split gives 8 shares or
- *   keeps at least 2048 of K per share.  Their FP32 partial sums go to the
- *   workspace and are added in a fixed order (deterministic) before the
- *   single rounding of C.  The result can differ from lt_gemm_f16_res in the
+ *   split the reduction (K) of output tiles over several workgroups: it has
+ *   room for the tiles of a last, at most half full, wave of 256x256 tiles, or
+ *   for all tiles of a launch of less than about one wave when the split gives
+ *   8 shares or keeps at least 2048 of K per share.  The call splits where
+ *   that is estimated to be faster than smaller tiles with the whole K, mostly
+ *   few tiles with a long K; the choice depends on the sizes, the leading
+ *   dimensions and beta != 0 only.  The FP32 partial sums go to the workspace
+ *   and are added in a fixed order (deterministic) before the single rounding
+ *   of C.  The result can differ from lt_gemm_f16_res in the
  *   last bits of those tiles (another FP32 summation order).  There is no
  *   split (workspace size 0) when N or K is not a multiple of 8.
  *   workspace: device memory owned by the caller, 16-byte aligned (else

@@ -713,9 +713,12 @@ constexpr int BKQ = 64;         // dQ: keys per slice (two 32-key groups)
 
 // NWQ waves per workgroup, one 32-query group each: 8 (256 queries), or 4
 // where those leave half the CUs without a workgroup (1024 tokens of 32
-// heads: 26.6 us with 8 waves, 24.6 with 4; every workgroup streams K, so more
-// of them than CUs lose: 2048 tokens of 40 heads 47.7 and 57 us).  LDS stages: two slices in flight
-// while one is used, three for the smaller workgroups.
+// heads: 26.6 us with 8 waves, 24.6 with 4).  Every workgroup streams K, so
+// more of them than CUs lose: 2048 tokens of 40 heads 47.7 and 57 us; between
+// half and all the CUs (forward and backward, 32 heads of 128) 4 waves win
+// under the causal mask, 1280 / 2048 tokens 106 / 188 us against 112 / 201, and
+// lose without it, 193 / 333 against 181 / 320.  LDS stages: two slices in
+// flight while one is used, three for the smaller workgroups.
 template <int D, int NWQ>
 struct DqSmem {
   using RT = RowTile<D, NWQ>;

@@ -1142,7 +1142,9 @@ splitk_reduce_kernel(const float* __restrict__ W, int S, int64_t Mt, int64_t Nt,
   *reinterpret_cast<half8*>(C + m * ldc + n) = o;
 }
 
-// one launch of one tile size; LDS stages as many as fit 160 KiB
+// one launch of one tile size; LDS stages: two of 64 KiB, three of 48, four of
+// 32, eight of 16 (five of 32 and ten of 16, all that fit 160 KiB, are level to
+// 7% slower: 1024 x 1024 x 4096 TN 20.4 us against 19.0)
 template <bool TA, bool TB, int EPI>
 hipError_t launch_tile(int tile, const GemmArgs& g, hipStream_t s) {
   switch (tile) {

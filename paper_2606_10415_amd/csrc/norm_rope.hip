@@ -6,8 +6,8 @@
 //     l, l + 64, ... of the row (coalesced), the sum of squares is a wave
 //     shuffle reduction; writes y = w * x * r (one rounding) and r.
 //       r = (mean_j x_j^2 + eps)^(-1/2)
-//   * rmsnorm_bwd: workgroups of 4 waves (at most 512), all of a workgroup on
-//     one row at a time; per row
+//   * rmsnorm_bwd: workgroups of 4 waves (at most 512), on one row at a time
+//     (rows of up to 1024 columns: two or four rows side by side); per row
 //       dx = r * w * g - r^3 * x / H * sum_j g_j w_j x_j   (+ residual R)
 //     with g, x and R read once, into registers, one row ahead.  Every thread
 //     keeps the FP32 partial of dw = sum_rows g * x * r for its columns; the
@@ -72,13 +72,14 @@ rmsnorm_fwd_kernel(const lt_half* __restrict__ X, int64_t ldx, const lt_half* __
 }
 
 // ---------------------------------------------------------------- backward
-// Workgroups of kBwdWaves waves, the whole workgroup on one row at a time: thread t owns the 16-byte chunks t, t + 256,
-// ... of every row, so its w and its FP32 dw partial stay in registers (KPT
-// chunks) and the workgroup's partial row needs no further sum.  HBM-bound
-// (g, x, R in, dx out): the next row's loads are in flight while the current
-// row's dot product goes through the waves (one barrier a row, sums in wave
-// order).  With one wave per row a row's 30 KB were loaded, reduced and
-// written in turn by 8 waves a CU: 4096 x 5120 took 52 us (3.2 TB/s), now 41.
+// Workgroups of kBwdWaves waves, the whole workgroup on one row at a time:
+// thread t owns the 16-byte chunks t, t + 256, ... of every row, so its w and
+// its FP32 dw partial stay in registers (KPT chunks) and the workgroup's
+// partial row needs no further sum.  HBM-bound (g, x, R in, dx out): the next
+// row's loads are in flight while the current row's dot product goes through
+// the waves (one barrier a row, sums in wave order).  With one wave per row a
+// row's 30 KB were loaded, reduced and written in turn by 8 waves a CU: 4096 x
+// 5120 took 52 us (3.2 TB/s), now 41.
 // Narrow rows would leave lanes idle: up to 512 (1024) columns a row takes one
 // (two) of the four waves, the groups take rows side by side and add their dw
 // partials through LDS at the end.
@@ -164,8 +165,9 @@ rmsnorm_bwd_kernel(const lt_half* __restrict__ dY, int64_t lddy, const lt_half* 
 
   // rows blockIdx.x, + gridDim.x, ...: the workgroups sweep the arrays together
   // (a contiguous range each: 43 us against 41 at 4096 x 5120; a third row in
-  // flight changes nothing).  Two rows per trip: two register sets, two reduction slots (a slot is written
-  // again only after the barrier of the row between).
+  // flight changes nothing).  Two rows per trip: two register sets, two
+  // reduction slots (a slot is written again only after the barrier of the row
+  // between).
   // Groups run the same number of steps (barriers inside); a group without a
   // row left repeats its last one with nothing stored and zero g.
   const int64_t step = (int64_t)gridDim.x * NG;

@@ -6,8 +6,8 @@
 
 namespace lt {
 
-// The split a workspace is sized for; whether a call with a workspace takes
-// it is decided by gemm_plan below.
+// The split a workspace is sized for.  gemm_plan below decides whether a call
+// with a workspace takes it; the size keeps room for it either way.
 bool gemm_splitk_tail(int64_t M, int64_t N, int64_t K, SplitTail* p) {
   // the geometry of the half-tile tail (256x256 tiles, one wave = 256 CUs),
   // with the last wave's K split so that its units fill about one wave; a
@@ -99,7 +99,9 @@ constexpr TileCost kTileCost[kNumGemmTiles] = {
     {0.25, 0.26, 0.02, {1.5, 3.0, 5.5}, 0.5, 1.2, 1.3},
 };
 constexpr double kLaunchUs = 4.0;             // a further launch in the stream
-constexpr double kPartialBytesPerUs = 9.0e6;  // split-K partials, written, then read
+// split-K partials, written, then read: above the memory's rate, as the 64 MiB
+// at most of them stay in the 256 MiB memory-side cache
+constexpr double kPartialBytesPerUs = 9.0e6;
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -135,8 +137,9 @@ double region_cost(int tile, const TileKind& k, bool reads_r, int64_t M, int64_t
 //     large tile would leave half empty;
 //   * the split-K plan, given a workspace: whole rounds, then the remaining
 //     tiles with K split; it pays where few tiles face a long K.
-// Larger tiles cost less per FLOP (the 256x256 tile's slice: 1.56 us, four
-// 128x128 slices: 2.4 us), smaller ones fill the CUs and their last round.
+// Larger tiles cost less per FLOP (the 256x256 tile's slice with every CU
+// busy: 1.58 us, four 128x128 slices: 2.4 us), smaller ones fill the CUs and
+// their last round.
 GemmPlan gemm_plan(int transA, int64_t M, int64_t N, int64_t K, int epi, bool reads_r, bool split_k,
                    bool split_rows) {
   const TileKind kind{transA != 0, split_rows, epi};
