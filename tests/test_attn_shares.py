@@ -89,6 +89,19 @@ def test_planned_shares():
         assert attn_shares(*case) == plan, case
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,shares", [
+    # a few percent of estimated gain is no reason to leave equal shares (of a
+    # ragged last tile's own number): backward and forward in proportion 124
+    # and 392 us, equal 115 and 374
+    (1, 1636, 16, 16, 128, [2] * 12 + [1]),
+    (1, 2975, 32, 8, 128, [4] * 11 + [2]),
+    # 20%: 122 us equal, 107 in proportion
+    (1, 2048, 40, 8, 128, [7, 6, 5, 4, 4, 3, 2, 1]),
+])
+def test_equal_shares_stay_unless_clearly_slower(B, S, Hq, Hkv, D, shares):
+    assert attn_shares(B, S, Hq, Hkv, D, True)[1] == shares
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("saved", [False, True], ids=["recomputed", "saved-P"])
 @pytest.mark.parametrize("B,S,Hq,Hkv,D,causal", [
