@@ -44,9 +44,9 @@ GEMM_TRAFFIC = {
     "workload": "llama2-7b",
     "layer": "paper",
     "fuse_swiglu": True,
-    "sources_sha256": "28b551bfcc85b63f527c7da3ddeff34891f1f5593ab9b9fe949b55c495b6b5ce",
-    "fetch_bytes_per_launch": 675429221,
-    "write_bytes_per_launch": 108471157,
+    "sources_sha256": "9ae8756e101ea4f72d4589216200c54078a366118075358419943f4e01bdaaa0",
+    "fetch_bytes_per_launch": 675748007,
+    "write_bytes_per_launch": 93673317,
 }
 GEMM_SOURCES = ("paper_2606_10415_amd/csrc/gemm_f16.hip", "paper_2606_10415_amd/csrc/common.hpp",
                 "paper_2606_10415_amd/csrc/plan.cpp")
